@@ -2542,13 +2542,13 @@ epic_status epic_image_backward(epic_ctx* x, const uint8_t* efield, int64_t n_ti
   if (x->cfg.precision != EPIC_FP32)
     return x->fail(EPIC_E_UNSUPPORTED, "the gain gradient runs on the float32 paths");
   DeviceGuard guard(x->device);
+  (void)hipGetLastError();               // an error of other code in this thread is not this call's
   if (!x->fused) return staged_backward(x, efield, n_time, gains, grad_image, grad_gains);
   if (use_cov_backward(x, efield, n_time)) return cov_backward(x, efield, n_time, gains, grad_image, grad_gains);
   const int C = x->cfg.n_chan;
   // work units per channel: samples, or (parity, sample) pairs at N = 128
   const int64_t upc = x->cfg.grid_n == 128 ? 2 * n_time : n_time;
   const int64_t total = (int64_t)C * upc;
-  (void)hipGetLastError();
   {
     epic::GradTableArgs ta;
     ta.grad_image = reinterpret_cast<const double2*>(grad_image);
