@@ -11,7 +11,7 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libepic.so")
-SOURCES = [os.path.join(PKG, "csrc", "epic.hip")]
+SOURCES = [os.path.join(PKG, "csrc", f) for f in ("epic.hip", "covar.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 

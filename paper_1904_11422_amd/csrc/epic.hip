@@ -18,8 +18,7 @@
 
 #include "dft.hpp"
 #include "fused.hpp"
-#include "covar.hpp"
-#include "covar_adjoint.hpp"
+#include "covar_launch.hpp"
 #include "staged.hpp"
 #include "adjoint.hpp"
 #include "split.hpp"
@@ -1440,20 +1439,10 @@ FusedGrid fused_grid(const epic_ctx* x, int64_t n_time, int max_team = kMaxTeam)
   return g;
 }
 
-constexpr int kCovMaxParts = 4;                       // time splits per channel at most
+using epic::covar::kCovMaxParts;
 
-// The fold's template for this context and `splits` time splits: f(kernel,
-// threads).
-template <typename F>
-void cov_fold_dispatch(const epic_ctx* x, int splits, F&& f) {
-#define EPIC_CF(PP, WW, DD)                                                                       \
-  if (x->cfg.n_pol == PP && x->wide == WW && x->cov_dense == DD) {                                \
-    if (splits == 1) f(epic::cov_fold_kernel<PP, WW, DD, 1>, epic::CovFold<PP, WW, DD>::NT);      \
-    else f(epic::cov_fold_kernel<PP, WW, DD, kCovMaxParts>, epic::CovFold<PP, WW, DD>::NT);       \
-  }
-  EPIC_CF(1, false, false) EPIC_CF(1, false, true) EPIC_CF(1, true, false) EPIC_CF(1, true, true)
-  EPIC_CF(2, false, false) EPIC_CF(2, false, true) EPIC_CF(2, true, false) EPIC_CF(2, true, true)
-#undef EPIC_CF
+epic::covar::Shape cov_shape(const epic_ctx* x, int splits) {
+  return {x->cfg.n_pol, x->wide, x->cov_dense, splits == 1};
 }
 
 constexpr size_t kCovWorkspace = (size_t)384 << 20;   // bytes of covariances at most
@@ -1641,9 +1630,7 @@ void build_cov(epic_ctx* x, const Geometry& g) {
   x->cov_ap = (A + epic::kCovTile - 1) / epic::kCovTile * epic::kCovTile;
   // shares per channel: whole rounds of resident workgroups, a share costing
   // its antennas and about 6 more (program, first stage, output)
-  int per_cu = 1;
-  cov_fold_dispatch(x, 1, [&](auto k, int nt) { per_cu = occupancy_blocks(k, nt); });
-  const int64_t slots = (int64_t)std::max(1, per_cu) * x->n_cu;
+  const int64_t slots = (int64_t)epic::covar::fold_blocks_per_cu(cov_shape(x, 1)) * x->n_cu;
   double best = 0;
   for (int n = 1; n <= 32 && n * 4 <= std::max(A, 4); ++n) {
     const double t = (double)(((int64_t)C * n + slots - 1) / slots) * ((A + n - 1) / n + 6);
@@ -1790,15 +1777,7 @@ epic::CovCorrArgs launch_cov_corr(epic_ctx* x, const CovPlan& p, const uint8_t* 
   a.n_split = p.splits;
   a.n_prod = n_prod;
   a.total = nc * p.splits * epic::cov_tiles(x->cov_ap / epic::kCovTile, P);
-  const bool vec = cov_vec(x, efield);
-  auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3((unsigned)a.total), dim3(256), 0, x->stream, a); };
-  if (P == 2) {
-    if (vec) go(epic::cov_corr_kernel<2, true>);
-    else go(epic::cov_corr_kernel<2, false>);
-  } else {
-    if (vec) go(epic::cov_corr_kernel<1, true>);
-    else go(epic::cov_corr_kernel<1, false>);
-  }
+  epic::covar::launch_corr(a, P, cov_vec(x, efield), x->stream);
   return a;
 }
 
@@ -1824,9 +1803,7 @@ epic_status run_cov(epic_ctx* x, const uint8_t* efield, int64_t n_time, const fl
     fa.n_split = ns;
     fa.n_chunk = x->cov_chunks;
     fa.total = nc * x->cov_chunks;
-    cov_fold_dispatch(x, ns, [&](auto k, int nt) {
-      hipLaunchKernelGGL(k, dim3((unsigned)fa.total), dim3(nt), 0, x->stream, fa);
-    });
+    epic::covar::launch_fold(fa, cov_shape(x, ns), x->stream);
     epic::CovImageArgs ia;
     ia.r = fa.r;
     ia.v = ca.v;
@@ -1841,8 +1818,7 @@ epic_status run_cov(epic_ctx* x, const uint8_t* efield, int64_t n_time, const fl
     ia.n_chunk = x->cov_chunks;
     ia.reset = reset ? 1 : 0;
     ia.transposed = x->transposed ? 1 : 0;
-    if (P == 2) hipLaunchKernelGGL(epic::cov_image_kernel<2>, dim3(3 * nc), dim3(512), 0, x->stream, ia);
-    else hipLaunchKernelGGL(epic::cov_image_kernel<1>, dim3(nc), dim3(512), 0, x->stream, ia);
+    epic::covar::launch_image(ia, P, nc, x->stream);
   }
   x->last_kernel = "cov_fold_kernel";
   mark_main_end(x);
@@ -1867,8 +1843,7 @@ epic_status cov_backward(epic_ctx* x, const uint8_t* efield, int64_t n_time, con
     ha.hat = x->cov_hat.as<float2>();
     ha.c0 = c0;
     ha.transposed = x->transposed ? 1 : 0;
-    if (P == 2) hipLaunchKernelGGL(epic::cov_hat_kernel<2>, dim3(4 * nc), dim3(512), 0, x->stream, ha);
-    else hipLaunchKernelGGL(epic::cov_hat_kernel<1>, dim3(nc), dim3(512), 0, x->stream, ha);
+    epic::covar::launch_hat(ha, P, nc, x->stream);
     epic::CovGradArgs ga;
     ga.v = ca.v;
     ga.gains = reinterpret_cast<const float2*>(gains);
@@ -1884,22 +1859,15 @@ epic_status cov_backward(epic_ctx* x, const uint8_t* efield, int64_t n_time, con
     ga.groups = x->cov_ggroups;
     ga.autos = x->autos ? 1 : 0;
     ga.total = nc * P * x->cov_gchunks;
-    auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3((unsigned)ga.total), dim3(512), 0, x->stream, ga); };
-#define EPIC_CG(PP, WW)                                                  \
-  if (P == PP && x->wide == WW) {                                        \
-    if (plan.splits == 1) go(epic::covar::adjoint_kernel<PP, WW, 1>);          \
-    else go(epic::covar::adjoint_kernel<PP, WW, kCovMaxParts>);                \
-  }
-    EPIC_CG(1, false) EPIC_CG(1, true) EPIC_CG(2, false) EPIC_CG(2, true)
-#undef EPIC_CG
+    epic::covar::launch_adjoint(ga, cov_shape(x, plan.splits), x->stream);
     epic::CovGradSumArgs sa;
     sa.part = ga.part;
     sa.grad = reinterpret_cast<float2*>(grad_gains);
-    sa.PA = x->PA;
+    sa.n_ant = A;
     sa.n_part = P * ga.n_chunk * ga.groups;
     sa.c0 = c0;
     sa.n = (int64_t)nc * x->PA;
-    hipLaunchKernelGGL(epic::cov_grad_sum_kernel, dim3((unsigned)((sa.n + 255) / 256)), dim3(256), 0, x->stream, sa);
+    epic::covar::launch_grad_sum(sa, P, x->stream);
   }
   x->last_kernel = "adjoint_kernel";
   mark_main_end(x);
