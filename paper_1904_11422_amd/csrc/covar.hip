@@ -15,10 +15,8 @@ namespace {
 // The fold's template for a shape: f(kernel, threads).
 template <typename F> void fold_dispatch(const Shape& s, F&& f) {
 #define EPIC_CF(PP, WW, DD)                                                                       \
-  if (s.n_pol == PP && s.wide == WW && s.dense == DD) {                                           \
-    if (s.one_split) f(cov_fold_kernel<PP, WW, DD, 1>, CovFold<PP, WW, DD>::NT);                  \
-    else f(cov_fold_kernel<PP, WW, DD, kCovMaxParts>, CovFold<PP, WW, DD>::NT);                   \
-  }
+  if (s.n_pol == PP && s.wide == WW && s.dense == DD)                                             \
+    f(cov_fold_kernel<PP, WW, DD>, CovFold<PP, WW, DD>::NT);
   EPIC_CF(1, false, false) EPIC_CF(1, false, true) EPIC_CF(1, true, false) EPIC_CF(1, true, true)
   EPIC_CF(2, false, false) EPIC_CF(2, false, true) EPIC_CF(2, true, false) EPIC_CF(2, true, true)
 #undef EPIC_CF
@@ -45,6 +43,10 @@ void launch_corr(const CovCorrArgs& a, int n_pol, bool vec, hipStream_t stream) 
   }
 }
 
+void launch_sum(const CovSumArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL(cov_sum_kernel, dim3((unsigned)((a.total + 255) / 256)), dim3(256), 0, stream, a);
+}
+
 void launch_fold(const CovFoldArgs& a, const Shape& s, hipStream_t stream) {
   fold_dispatch(s, [&](auto k, int nt) { hipLaunchKernelGGL(k, dim3((unsigned)a.total), dim3(nt), 0, stream, a); });
 }
@@ -61,11 +63,8 @@ void launch_hat(const CovHatArgs& a, int n_pol, int n_chan, hipStream_t stream) 
 
 void launch_adjoint(const CovGradArgs& a, const Shape& s, hipStream_t stream) {
   auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3((unsigned)a.total), dim3(512), 0, stream, a); };
-#define EPIC_CG(PP, WW)                                                  \
-  if (s.n_pol == PP && s.wide == WW) {                                   \
-    if (s.one_split) go(adjoint_kernel<PP, WW, 1>);                      \
-    else go(adjoint_kernel<PP, WW, kCovMaxParts>);                       \
-  }
+#define EPIC_CG(PP, WW) \
+  if (s.n_pol == PP && s.wide == WW) go(adjoint_kernel<PP, WW>);
   EPIC_CG(1, false) EPIC_CG(1, true) EPIC_CG(2, false) EPIC_CG(2, true)
 #undef EPIC_CG
 }

@@ -13,6 +13,7 @@
 // sampled at N points, so the circular autocorrelation is all it can see.
 //
 //   cov_corr_kernel   V of a channel, 128 x 128 antennas per workgroup;
+//   cov_sum_kernel    where its samples are split, the splits added;
 //   cov_fold_kernel   R of a share of a channel's antennas b (float32 sums, as
 //                     the fused kernels' block sums);
 //   cov_image_kernel  the shares summed, transformed and written in float64.
@@ -244,6 +245,30 @@ __global__ __launch_bounds__(256, 2) void cov_corr_kernel(CovCorrArgs a) {
   }
 }
 
+struct CovSumArgs {
+  int2* v;                  // cov_corr_kernel's output
+  int64_t n;                // values of a channel and split (n_prod ap^2)
+  int n_split;
+  int64_t total;            // pairs of values: channels * n / 2
+};
+
+// Time splits of V added into the first, so that what follows reads one plane
+// per product whatever the split (holding up to four in flight cost the fold and
+// the gradient 11 to 29 spilled registers, reloaded behind the prefetch of V).
+// Bound: HBM, one pass.  Only calls of few channels split.
+__global__ static __launch_bounds__(256) void cov_sum_kernel(CovSumArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.total) return;
+  const int64_t h = a.n / 2, cl = i / h;
+  int4* v = reinterpret_cast<int4*>(a.v + cl * a.n_split * a.n) + i % h;
+  int4 s = v[0];
+  for (int k = 1; k < a.n_split; ++k) {
+    const int4 x = v[k * h];
+    s = make_int4(s.x + x.x, s.y + x.y, s.z + x.z, s.w + x.w);
+  }
+  v[0] = s;
+}
+
 // Antenna b of a channel, in the order the fold takes them (by column): its
 // first tap's cell in the programs' (possibly transposed) aperture and its
 // kernel as row and column factors.
@@ -274,7 +299,7 @@ template <int STEPS> struct CovProgLane {
 };
 
 struct CovFoldArgs {
-  const int2* v;            // cov_corr_kernel's output
+  const int2* v;            // cov_corr_kernel's output, the splits added
   const float2* gains;      // [C][P][A]
   const CovProgHead* head;  // [C][waves]
   const void* prog;         // CovProgLane [C][waves][64]
@@ -341,7 +366,7 @@ template <int N, typename F> __device__ __forceinline__ void static_while(F&& f)
   static_while_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <int P, bool WIDE, bool DENSE, int NS>
+template <int P, bool WIDE, bool DENSE>
 __global__ __launch_bounds__((WIDE ? 1024 : 512), (DENSE && !WIDE ? 2 : 4)) void cov_fold_kernel(CovFoldArgs a) {
   using S = CovFold<P, WIDE, DENSE>;
   constexpr int N = S::N, NT = S::NT, MAXA = S::MAXA, kCovSteps = S::STEPS, NV = S::NV, RS = S::RS, VS = S::VS, LR = S::LR, G = S::G;
@@ -389,9 +414,9 @@ __global__ __launch_bounds__((WIDE ? 1024 : 512), (DENSE && !WIDE ? 2 : 4)) void
   const int plane = ap * ap;
   const int64_t vsplit = (int64_t)CovShape<P>::NPROD * plane * sizeof(int2);
   const char* vc = reinterpret_cast<const char*>(a.v) + cl * a.n_split * vsplit;
-  // V of a step: loaded two steps before it is staged, added up when staged
+  // V of a step: loaded two steps before it is staged
   struct Pre {
-    int2 v[NE][NS];
+    int2 v[NE];
     int b[NB];                          // antennas of the step (-1: none)
   };
   Pre pre0, pre1;
@@ -414,9 +439,7 @@ __global__ __launch_bounds__((WIDE ? 1024 : 512), (DENSE && !WIDE ? 2 : 4)) void
       const int b = NB == 1 ? p.b[0] : v ? p.b[NB - 1] : p.b[0];
       const uint32_t col = __builtin_amdgcn_readfirstlane((P == 2 ? v * plane : 0) + cov_slot(b < 0 ? 0 : b) * ap);
       const uint32_t off = 8u * (col + sofs[i] + (vec[i] < NV ? tid : 0));
-#pragma unroll
-      for (int s = 0; s < NS; ++s)
-        p.v[i][s] = *reinterpret_cast<const int2*>(vc + (NS == 1 || s < a.n_split ? s : 0) * vsplit + off);
+      p.v[i] = *reinterpret_cast<const int2*>(vc + off);
     }
     lookup(it + 1);
   };
@@ -428,10 +451,7 @@ __global__ __launch_bounds__((WIDE ? 1024 : 512), (DENSE && !WIDE ? 2 : 4)) void
       const int b = NB == 1 ? p.b[0] : v ? p.b[NB - 1] : p.b[0];
       const int ant = cov_ant(tid + sofs[i]);
       if (ant >= A) continue;
-      int2 val = p.v[i][0];
-#pragma unroll
-      for (int s = 1; s < NS; ++s)
-        if (s < a.n_split) val = make_int2(val.x + p.v[i][s].x, val.y + p.v[i][s].y);
+      int2 val = p.v[i];
       // the a = b terms are added (or left out) by cov_image_kernel, in float64;
       // b < 0: the last step of a share at P = 1 may have one antenna only
       if (b == ant || b < 0) val = make_int2(0, 0);
@@ -773,11 +793,7 @@ __global__ __launch_bounds__(512) void cov_image_kernel(CovImageArgs a) {
       const CovAnt w = a.ants[(int64_t)c * a.n_ant + i];
       const int64_t pp = (int64_t)a.ap * a.ap, o = (int64_t)cov_slot(w.ant) * (a.ap + 1);
       const int2* v = a.v + (int64_t)cl * a.n_split * CovShape<P>::NPROD * pp + o;
-      int2 v0 = make_int2(0, 0);
-      for (int s = 0; s < a.n_split; ++s, v += CovShape<P>::NPROD * pp) {
-        const int2 x = v[(plane == 1 ? 2 : plane == 2 ? 1 : 0) * pp];
-        v0 = make_int2(v0.x + x.x, v0.y + x.y);
-      }
+      const int2 v0 = v[(plane == 1 ? 2 : plane == 2 ? 1 : 0) * pp];
       const float2* g = a.gains + (int64_t)c * P * a.n_ant + w.ant;
       const float2 gp = g[plane == 2 ? a.n_ant : 0], gq = g[plane >= 1 ? a.n_ant : 0];
       const double gr = (double)gp.x * gq.x + (double)gp.y * gq.y, gi = (double)gp.y * gq.x - (double)gp.x * gq.y;

@@ -7,15 +7,15 @@ namespace epic {
 namespace covar {
 
 // Shape of a launch: polarisations, wide block, the fold's variant for many
-// antennas or crowded cells, one time split or up to kCovMaxParts.
+// antennas or crowded cells.
 struct Shape {
   int n_pol;
-  bool wide, dense, one_split;
+  bool wide, dense;
 };
-constexpr int kCovMaxParts = 4;       // time splits per channel at most
 
 int fold_blocks_per_cu(const Shape& s);
 void launch_corr(const CovCorrArgs& a, int n_pol, bool vec, hipStream_t stream);
+void launch_sum(const CovSumArgs& a, hipStream_t stream);
 void launch_fold(const CovFoldArgs& a, const Shape& s, hipStream_t stream);
 void launch_image(const CovImageArgs& a, int n_pol, int n_chan, hipStream_t stream);
 void launch_hat(const CovHatArgs& a, int n_pol, int n_chan, hipStream_t stream);

@@ -1439,11 +1439,9 @@ FusedGrid fused_grid(const epic_ctx* x, int64_t n_time, int max_team = kMaxTeam)
   return g;
 }
 
-using epic::covar::kCovMaxParts;
+constexpr int kCovMaxParts = 4;                       // time splits per channel at most
 
-epic::covar::Shape cov_shape(const epic_ctx* x, int splits) {
-  return {x->cfg.n_pol, x->wide, x->cov_dense, splits == 1};
-}
+epic::covar::Shape cov_shape(const epic_ctx* x) { return {x->cfg.n_pol, x->wide, x->cov_dense}; }
 
 constexpr size_t kCovWorkspace = (size_t)384 << 20;   // bytes of covariances at most
 
@@ -1630,7 +1628,7 @@ void build_cov(epic_ctx* x, const Geometry& g) {
   x->cov_ap = (A + epic::kCovTile - 1) / epic::kCovTile * epic::kCovTile;
   // shares per channel: whole rounds of resident workgroups, a share costing
   // its antennas and about 6 more (program, first stage, output)
-  const int64_t slots = (int64_t)epic::covar::fold_blocks_per_cu(cov_shape(x, 1)) * x->n_cu;
+  const int64_t slots = (int64_t)epic::covar::fold_blocks_per_cu(cov_shape(x)) * x->n_cu;
   double best = 0;
   for (int n = 1; n <= 32 && n * 4 <= std::max(A, 4); ++n) {
     const double t = (double)(((int64_t)C * n + slots - 1) / slots) * ((A + n - 1) / n + 6);
@@ -1678,7 +1676,9 @@ void build_cov(epic_ctx* x, const Geometry& g) {
   x->cov = true;
 }
 
-// Time splits of the covariance kernel.
+// Time splits of the covariance kernel: its rounds of resident workgroups (0.9 us
+// per stage of 64 samples, 6 stages' worth of start and output) against the
+// planes written, read, added and read again at about 4 TB/s and one more launch.
 int cov_splits(const epic_ctx* x, int64_t n_time) {
   const int64_t tiles = epic::cov_tiles(x->cov_ap / epic::kCovTile, x->cfg.n_pol);
   const int64_t slots = 2 * (int64_t)x->n_cu;
@@ -1688,7 +1688,7 @@ int cov_splits(const epic_ctx* x, int64_t n_time) {
   for (int64_t n = need; n <= kCovMaxParts; ++n) {
     const int64_t stages = ((n_time + n - 1) / n + epic::kCovStage - 1) / epic::kCovStage;
     const double t = (double)((x->cfg.n_chan * tiles * n + slots - 1) / slots) * (stages + 6) * 0.9 +
-                     (double)n * x->cfg.n_chan * cov_v_bytes(x) / 2.0e6;
+                     (n == 1 ? 2.0 : 2.0 * n + 2.0) * x->cfg.n_chan * cov_v_bytes(x) / 4.0e6 + (n == 1 ? 0.0 : 6.0);
     if (n == need || t < best) {
       best = t;
       best_n = (int)n;
@@ -1761,7 +1761,7 @@ CovPlan cov_plan(const epic_ctx* x, int64_t n_time, int n_prod) {
   return p;
 }
 
-// Covariances of channels c0 .. c0 + nc - 1 into the workspace.
+// Covariances of channels c0 .. c0 + nc - 1 into the workspace, time splits added.
 epic::CovCorrArgs launch_cov_corr(epic_ctx* x, const CovPlan& p, const uint8_t* efield, int64_t n_time, int c0,
                                   int nc, int n_prod) {
   const int P = x->cfg.n_pol, A = x->cfg.n_ant;
@@ -1778,6 +1778,14 @@ epic::CovCorrArgs launch_cov_corr(epic_ctx* x, const CovPlan& p, const uint8_t* 
   a.n_prod = n_prod;
   a.total = nc * p.splits * epic::cov_tiles(x->cov_ap / epic::kCovTile, P);
   epic::covar::launch_corr(a, P, cov_vec(x, efield), x->stream);
+  if (p.splits > 1) {
+    epic::CovSumArgs sa;
+    sa.v = a.v;
+    sa.n = (int64_t)n_prod * a.ap * a.ap;
+    sa.n_split = p.splits;
+    sa.total = nc * sa.n / 2;
+    epic::covar::launch_sum(sa, x->stream);
+  }
   return a;
 }
 
@@ -1803,7 +1811,7 @@ epic_status run_cov(epic_ctx* x, const uint8_t* efield, int64_t n_time, const fl
     fa.n_split = ns;
     fa.n_chunk = x->cov_chunks;
     fa.total = nc * x->cov_chunks;
-    epic::covar::launch_fold(fa, cov_shape(x, ns), x->stream);
+    epic::covar::launch_fold(fa, cov_shape(x), x->stream);
     epic::CovImageArgs ia;
     ia.r = fa.r;
     ia.v = ca.v;
@@ -1859,7 +1867,7 @@ epic_status cov_backward(epic_ctx* x, const uint8_t* efield, int64_t n_time, con
     ga.groups = x->cov_ggroups;
     ga.autos = x->autos ? 1 : 0;
     ga.total = nc * P * x->cov_gchunks;
-    epic::covar::launch_adjoint(ga, cov_shape(x, plan.splits), x->stream);
+    epic::covar::launch_adjoint(ga, cov_shape(x), x->stream);
     epic::CovGradSumArgs sa;
     sa.part = ga.part;
     sa.grad = reinterpret_cast<float2*>(grad_gains);
