@@ -9,16 +9,35 @@
 #include "covar_launch.hpp"
 
 namespace epic {
+
+// Time splits of V added into the first, so that what follows reads one plane
+// per product whatever the split (holding up to four in flight cost the fold and
+// the gradient 11 to 29 spilled registers, reloaded behind the prefetch of V).
+// Bound: HBM, one pass.  Only calls of few channels split.
+__global__ __launch_bounds__(256) void cov_sum_kernel(CovSumArgs a) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= a.total) return;
+  const int64_t h = a.n / 2, cl = i / h;
+  int4* v = reinterpret_cast<int4*>(a.v + cl * a.n_split * a.n) + i % h;
+  int4 s = v[0];
+  for (int k = 1; k < a.n_split; ++k) {
+    const int4 x = v[k * h];
+    s = make_int4(s.x + x.x, s.y + x.y, s.z + x.z, s.w + x.w);
+  }
+  v[0] = s;
+}
+
 namespace covar {
 namespace {
 
 // The fold's template for a shape: f(kernel, threads).
 template <typename F> void fold_dispatch(const Shape& s, F&& f) {
-#define EPIC_CF(PP, WW, DD)                                                                       \
-  if (s.n_pol == PP && s.wide == WW && s.dense == DD)                                             \
-    f(cov_fold_kernel<PP, WW, DD>, CovFold<PP, WW, DD>::NT);
-  EPIC_CF(1, false, false) EPIC_CF(1, false, true) EPIC_CF(1, true, false) EPIC_CF(1, true, true)
-  EPIC_CF(2, false, false) EPIC_CF(2, false, true) EPIC_CF(2, true, false) EPIC_CF(2, true, true)
+#define EPIC_CF(PP, WW, KK)                                                                       \
+  if (s.n_pol == PP && s.wide == WW && s.kind == KK)                                              \
+    f(cov_fold_kernel<PP, WW, KK>, CovFold<PP, WW, KK>::NT);
+  EPIC_CF(1, false, kCovPlain) EPIC_CF(1, false, kCovMany) EPIC_CF(1, false, kCovCrowded)
+  EPIC_CF(2, false, kCovPlain) EPIC_CF(2, false, kCovMany) EPIC_CF(2, false, kCovCrowded)
+  EPIC_CF(1, true, kCovPlain) EPIC_CF(1, true, kCovMany) EPIC_CF(2, true, kCovPlain) EPIC_CF(2, true, kCovMany)
 #undef EPIC_CF
 }
 
@@ -48,7 +67,7 @@ void launch_sum(const CovSumArgs& a, hipStream_t stream) {
 }
 
 void launch_fold(const CovFoldArgs& a, const Shape& s, hipStream_t stream) {
-  fold_dispatch(s, [&](auto k, int nt) { hipLaunchKernelGGL(k, dim3((unsigned)a.total), dim3(nt), 0, stream, a); });
+  fold_dispatch(s, [&](auto k, int nt) { hipLaunchKernelGGL(k, dim3((unsigned)a.W), dim3(nt), 0, stream, a); });
 }
 
 void launch_image(const CovImageArgs& a, int n_pol, int n_chan, hipStream_t stream) {

@@ -14,9 +14,8 @@
 //
 //   cov_corr_kernel   V of a channel, 128 x 128 antennas per workgroup;
 //   cov_sum_kernel    where its samples are split, the splits added;
-//   cov_fold_kernel   R of a share of a channel's antennas b (float32 sums, as
-//                     the fused kernels' block sums);
-//   cov_image_kernel  the shares summed, transformed and written in float64.
+//   cov_fold_kernel   R of a range of a channel's antennas b, in float64;
+//   cov_image_kernel  the ranges' sums added, transformed and written, in float64.
 #pragma once
 #include <type_traits>
 #include <utility>
@@ -252,31 +251,19 @@ struct CovSumArgs {
   int64_t total;            // pairs of values: channels * n / 2
 };
 
-// Time splits of V added into the first, so that what follows reads one plane
-// per product whatever the split (holding up to four in flight cost the fold and
-// the gradient 11 to 29 spilled registers, reloaded behind the prefetch of V).
-// Bound: HBM, one pass.  Only calls of few channels split.
-__global__ static __launch_bounds__(256) void cov_sum_kernel(CovSumArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= a.total) return;
-  const int64_t h = a.n / 2, cl = i / h;
-  int4* v = reinterpret_cast<int4*>(a.v + cl * a.n_split * a.n) + i % h;
-  int4 s = v[0];
-  for (int k = 1; k < a.n_split; ++k) {
-    const int4 x = v[k * h];
-    s = make_int4(s.x + x.x, s.y + x.y, s.z + x.z, s.w + x.w);
-  }
-  v[0] = s;
-}
-
 // Antenna b of a channel, in the order the fold takes them (by column): its
 // first tap's cell in the programs' (possibly transposed) aperture and its
 // kernel as row and column factors.
 struct __align__(16) CovAnt {
-  int ant, row, col, pad0;
-  float wr[4];              // weights of rows row .. row + 2
-  float wc[4];              // weights of columns col .. col + 2
+  int ant, row, col;
+  int voff;                 // its column in a plane of V, cov_slot(ant) * ap
+  double wr[3];             // weights of rows row .. row + 2
+  double wc[3];             // weights of columns col .. col + 2
+  float fr[3], fc[3];       // the same, rounded (the gradient's)
+  float pad1[2];
 };
+
+constexpr int kCovAntsPast = 16;    // entries past the table that the fold's look-ahead may read
 
 // Gridding program of the fold, per channel and wave: a wave grids RPW whole
 // consecutive rows, its cells dealt to "slots" of 64 (one per lane) by number of
@@ -285,17 +272,18 @@ struct __align__(16) CovAnt {
 // and store its cells; cells of no antenna are never written and stay zero.
 // Padding reads a zero slot of E'.  Per lane: the cells' byte offsets and the
 // steps' E' byte offsets, 16 bits each, and the steps' weights, all of it in
-// registers for the whole share (a step read from memory in the loop would wait
-// behind the prefetch of V).
-constexpr int kCovSlots = 4;        // slots of a wave at most
+// registers for the whole range (a step read from memory in the loop would wait
+// behind the prefetch of V).  A weight is the float64 product of the factors
+// that the fold multiplies by on b's side: R is Hermitian in d to float64
+// rounding only if the two sides agree, and half of it is taken from the other.
 struct CovProgHead {
   uint32_t row_lo, row_hi;          // aperture rows of the wave
   uint32_t steps, ends;
 };
-template <int STEPS> struct CovProgLane {
-  uint32_t cell[kCovSlots / 2];
+template <int STEPS, int SLOTS> struct CovProgLane {
+  uint32_t cell[SLOTS > 2 ? 2 : 1];
   uint32_t e[STEPS / 2];
-  float w[STEPS];
+  double w[STEPS];
 };
 
 struct CovFoldArgs {
@@ -303,60 +291,65 @@ struct CovFoldArgs {
   const float2* gains;      // [C][P][A]
   const CovProgHead* head;  // [C][waves]
   const void* prog;         // CovProgLane [C][waves][64]
-  const CovAnt* ants;       // [C][A]
-  float2* r;                // [channel - c0][chunk][CovFold rows][64]
+  const CovAnt* ants;       // [C][A], and kCovAntsPast more that may be read
+  double2* r;               // [workgroup + channel group][CovFold::ROWS][64]
   int n_ant, ap;
-  int c0, n_split, n_chunk;
-  int total;                // workgroups: channels * n_chunk
+  int c0, n_split;
+  int W;                    // workgroups
+  int64_t units;            // channels * groups * antennas
 };
 
-// Shape of the fold: NV aperture grids at a time (P = 2: the columns XX, YY and
-// XY of one antenna b; P = 1: XX of two antennas), R rows and W columns each,
-// lanes along the columns (LR lanes per row) and "units" of LR lanes along d's
-// rows, four rows of d per group.  XX and YY need half of the plane of d
-// (R(-d) = conj R(d)): rows 0 .. 31 for XX and 0 .. -31 for YY, row 32
-// riding in row 0's imaginary part (both are Hermitian in d's column alone,
-// which tells them apart).  Of M_b they read only the rows at or past b's first
-// (XX) or up to its last (YY), so a wave grids for one b mostly one of the two.
-// DENSE: more than 256 antennas, or more steps than the registers of the
-// others hold.
-// The wide block's grids need twice the LDS: one workgroup of 1024 threads per
-// CU instead of two of 512 (16 waves either way).
-template <int P, bool WIDE, bool DENSE> struct CovFold {
-  static constexpr int N = 64, NT = WIDE ? 1024 : 512, NW = NT / 64;
-  static constexpr int MAXA = DENSE ? 512 : 256;
-  static constexpr int STEPS = DENSE && !WIDE ? 24 : 12;     // program steps of a wave at most
-  static constexpr int NV = P == 2 ? 3 : 2;
+// The fold's units, (channel, group of sets, antenna b) in that order, are cut
+// into W consecutive ranges of equal length, one per workgroup; what a workgroup
+// adds to channel group cg goes to slot w + cg (a boundary of either kind moves
+// on by one).  First workgroup of the group's and its slots:
+__host__ __device__ __forceinline__ int cov_owner(int64_t unit, int64_t units, int W) {
+  return (int)(((unit + 1) * W - 1) / units);
+}
+
+// Shape of the fold: one workgroup of 1024 threads per CU and NV aperture grids at
+// a time, R rows and W columns each, lanes along the columns (LR lanes per row)
+// and "units" of LR lanes along d's rows, two rows of d per unit: the sums take
+// 24 registers of a thread's 128, the program 36.  The products come in sets:
+// Half the grid (two grids, 64 rows of d):
+//   set 0  half planes of d: at P = 2 XX and YY of one antenna b, at P = 1 XX of
+//          two;
+//   set 1  (P = 2) the whole plane of XY, of two antennas b one after the other.
+// Wide block (one grid, whose row takes a wave; 32 rows of d): XX, YY, and the
+// halves d = 0 .. 31 and -32 .. -1 of XY; sets 0 and 2, 1 and 3 make a group.
+// A workgroup makes all sets of a group for its antennas, so that ranges of equal
+// length take equal time whatever a set costs.
+// XX and YY need half of the plane of d (R(-d) = conj R(d)): rows 0 .. 31 for XX
+// and 0 .. -31 for YY, row 32 riding in row 0's imaginary part (both are
+// Hermitian in d's column alone, which tells them apart).  Of M_b a half plane
+// reads only the rows at or past b's first (d >= 0) or up to its last (d <= 0),
+// so about half of the waves grid for it.
+// KIND: kCovMany, more than 256 antennas; kCovCrowded, more steps than the
+// registers of the others hold (some of the program spills to scratch memory).
+enum { kCovPlain, kCovMany, kCovCrowded };
+template <int P, bool WIDE, int KIND> struct CovFold {
+  static constexpr int N = 64, NT = 1024, NW = NT / 64;
+  static constexpr int MAXA = KIND == kCovPlain ? 256 : 512;
+  static constexpr int STEPS = KIND == kCovCrowded ? 24 : 12;     // program steps of a wave at most
+  static constexpr int SLOTS = WIDE ? 4 : 1;                 // slots of a wave at most
+  static constexpr int NV = WIDE ? 1 : 2;
+  static constexpr int SETS = P == 1 ? 1 : WIDE ? 4 : 2;
+  static constexpr int GROUPS = P == 2 && WIDE ? 2 : 1;      // of sets
+  static constexpr int SROWS = 32 * NV;                      // rows of r per set
+  static constexpr int ROWS = SETS / GROUPS * SROWS;         // ... and slot
   static constexpr int R = WIDE ? FusedShape<64>::HW : 32;   // rows of a grid
   static constexpr int W = WIDE ? 48 : 32;                   // columns of a grid
-  static constexpr int RS = W + 1;                           // row stride; WIDE: column 48 stays zero
-  static constexpr int PADR = 5;                             // zero rows around each grid
+  static constexpr int RS = WIDE ? W + 1 : W + 4;            // row stride; column W stays zero
+  static constexpr int RU = 2;                               // rows of d per unit
+  static constexpr int PADR = RU + 1;                        // zero rows around each grid
   static constexpr int VS = (R + PADR) * RS;                 // grid stride
   static constexpr int MSIZE = PADR * RS + NV * VS;
+  static constexpr int ES = MAXA + 16;                       // E' of one grid, with 16 zero slots
   static constexpr int LR = WIDE ? 64 : 32;
-  static constexpr int UNITS = NT / LR;
-  static constexpr int HG = 16 / UNITS;                      // half-plane groups per unit (XX | YY)
-  static constexpr int FG = P == 2 ? 16 / UNITS : 0;         // full-plane groups per unit (XY)
-  static constexpr int G = HG + FG;
-  static constexpr int ROWS = P == 2 ? 128 : 64;             // rows of r: half planes, then XY
+  static constexpr int HU = 32 / RU;                         // units of 32 rows of d
+  static_assert(NT / LR * RU == SROWS, "a unit per two rows");
 };
 
-// Bound: LDS (gridding: about 2.25 reads of E' per cell and grid, gathered)
-// and the vector ALU.  A channel costs A passes of three grids, whatever T is.
-// The workgroup takes the antennas b of its share in column order.  Per b:
-// E'[a] = g_a conj(g_b) V_ab is staged, gridded with the channel's program
-// (held in registers for the whole share), and folded into R: a thread owns
-// one aperture column and four rows of d per group, forms the row taps of M_b
-// at its rows, and adds them, times the three column taps, to its sums Q_0 ..
-// Q_2 of the aperture columns col .. col + 2.  When the next antenna starts at
-// the next column, Q_0 moves one lane on into Q_1 (the same d), so a sum stays
-// in registers until its last term and R is written once.
-// 132 channels of 256 dual-pol antennas: 165 us (vector ALU 50 %, LDS 60 %; the
-// direct kernel takes 1173 us at T = 1000); with the direct kernels' programs,
-// whose lanes end their cells one by one, 340; with the steps past the eighth
-// read from memory 418; with the antennas' table read by vector loads 338.
-// The wide block: 305 us as one workgroup of 1024 threads, 349 as 512 threads and
-// one grid buffer (direct: 1752 us at T = 1250).
 // f(0), f(1), .. f(N - 1) with compile-time indices, until one returns false.
 template <typename F, int... I>
 __device__ __forceinline__ void static_while_impl(F&& f, std::integer_sequence<int, I...>) {
@@ -366,263 +359,320 @@ template <int N, typename F> __device__ __forceinline__ void static_while(F&& f)
   static_while_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-template <int P, bool WIDE, bool DENSE>
-__global__ __launch_bounds__((WIDE ? 1024 : 512), (DENSE && !WIDE ? 2 : 4)) void cov_fold_kernel(CovFoldArgs a) {
-  using S = CovFold<P, WIDE, DENSE>;
-  constexpr int N = S::N, NT = S::NT, MAXA = S::MAXA, kCovSteps = S::STEPS, NV = S::NV, RS = S::RS, VS = S::VS, LR = S::LR, G = S::G;
-  constexpr int ESF = MAXA + 16;
+// The value of the lane before (DPP wave shift right by one, 0x138, or rotation,
+// 0x13C: the first lane keeps its own, or takes the last one's).
+template <int CTRL> __device__ __forceinline__ double lane_before(double v) {
+  const int lo = __double2loint(v), hi = __double2hiint(v);
+  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false),
+                          __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false));
+}
+
+// Antennas b0 .. b1 - 1 (in column order) of channel a.c0 + cl, one set, into
+// rout.  Eb, Mb: E' and the grids in LDS, two of each.
+template <int P, int SET, bool WIDE, int KIND>
+__device__ __forceinline__ void cov_fold_body(const CovFoldArgs& a, double2* const lds, double2* const rout, int cl,
+                                              int b0, int b1) {
+  using S = CovFold<P, WIDE, KIND>;
+  constexpr int N = S::N, NT = S::NT, MAXA = S::MAXA, NV = S::NV, RS = S::RS, VS = S::VS, LR = S::LR, ES = S::ES, RU = S::RU;
   constexpr int NE = (NV * MAXA + NT - 1) / NT;
   constexpr int GB = 2;                 // steps whose reads are in flight together
-  __shared__ __align__(16) float2 lds[2 * NV * ESF + 2 * S::MSIZE + P * MAXA];
-  float2* const Eb = lds;
-  float2* const Mb = lds + 2 * NV * ESF;
-  float2* const Gl = Mb + 2 * S::MSIZE;       // the channel's gains
+  constexpr int NB = WIDE || (P == 2 && SET == 0) ? 1 : 2;   // antennas b per step
+  constexpr bool XY = SET >= (WIDE ? 2 : 1);
+  constexpr bool YYSET = WIDE && SET == 1;                   // YY alone
+  constexpr bool PAIR = !WIDE && !XY;                        // each half of the units has a grid of its own
   const int tid = threadIdx.x, lane = tid & 63;
-  const int logical = wg_range_index(blockIdx.x, a.total, 1);
-  const int cl = logical / a.n_chunk, ch = logical % a.n_chunk, c = a.c0 + cl;
+  const int c = a.c0 + cl;
   const int A = a.n_ant, ap = a.ap;
-  const int b0 = (int)((int64_t)ch * A / a.n_chunk), b1 = (int)((int64_t)(ch + 1) * A / a.n_chunk);
-  const int n_it = P == 2 ? b1 - b0 : (b1 - b0 + 1) / 2;
+  const int n_it = (b1 - b0 + NB - 1) / NB;
+  double2 *const Eb = lds, *const Mb = lds + 2 * NV * ES;
   // in the constant address space: uniform indices load through the scalar
   // cache, off the vector memory counter that the prefetch of V waits on
   using ConstAnt = const __attribute__((address_space(4))) CovAnt;
   ConstAnt* ants = (ConstAnt*)(a.ants + (int64_t)c * A);
-
-  for (int i = tid; i < 2 * NV * ESF + 2 * S::MSIZE; i += NT) lds[i] = make_float2(0.f, 0.f);
-  for (int i = tid; i < P * A; i += NT) Gl[i < A ? i : MAXA + i - A] = a.gains[(int64_t)c * P * A + i];
+  using ConstGain = const __attribute__((address_space(4))) float2;
+  ConstGain* gains = (ConstGain*)(a.gains + (int64_t)c * P * A);
 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const CovProgHead head = a.head[c * S::NW + wave];
-  const CovProgLane<S::STEPS> prog =
-      reinterpret_cast<const CovProgLane<S::STEPS>*>(a.prog)[(int64_t)(c * S::NW + wave) * 64 + lane];
-  const int row_lo = head.row_lo, row_hi = head.row_hi;
+  CovProgHead head = a.head[c * S::NW + wave];
+  head.steps = __builtin_amdgcn_readfirstlane(head.steps);
+  head.ends = __builtin_amdgcn_readfirstlane(head.ends);
+  const CovProgLane<S::STEPS, S::SLOTS> prog =
+      reinterpret_cast<const CovProgLane<S::STEPS, S::SLOTS>*>(a.prog)[(int64_t)(c * S::NW + wave) * 64 + lane];
+  // E' offsets unpacked (opaque: else they are unpacked at every step), where
+  // there are registers for it
+  constexpr bool UNPACK = KIND == kCovPlain;
+  uint32_t eoff[UNPACK ? S::STEPS : 1];
+  if constexpr (UNPACK) {
+#pragma unroll
+    for (int i = 0; i < S::STEPS; ++i) {
+      eoff[i] = i & 1 ? prog.e[i / 2] >> 16 : prog.e[i / 2] & 0xFFFFu;
+      asm volatile("" : "+v"(eoff[i]));
+    }
+  }
+  const int row_lo = __builtin_amdgcn_readfirstlane(head.row_lo), row_hi = __builtin_amdgcn_readfirstlane(head.row_hi);
 
-  // staging: element e = tid + NT i of the NV columns of V; a wave's 64 are in
+  // staging: element e = tid + NT i of the columns of V; a wave's 64 are in
   // one column (ap is a multiple of 128), so that all but the place in the
   // column and the gain of a is uniform
-  constexpr int NB = P == 2 ? 1 : NV;   // antennas b per step
   int vec[NE], sofs[NE];                // element i: its column, and its place less tid
+  float2 ga[NE];                        // its gain
 #pragma unroll
   for (int i = 0; i < NE; ++i) {
     const int e = tid + NT * i;
-    vec[i] = __builtin_amdgcn_readfirstlane((e >= ap) + (e >= 2 * ap) + (e >= 3 * ap));
-    sofs[i] = __builtin_amdgcn_readfirstlane(NT * i - vec[i] * ap);
-    if (vec[i] >= NV) sofs[i] = 0;
+    vec[i] = __builtin_amdgcn_readfirstlane((e >= ap) + (e >= 2 * ap));
+    sofs[i] = vec[i] < NV ? __builtin_amdgcn_readfirstlane(NT * i - vec[i] * ap) : 0;
+    const int ant = cov_ant(tid + sofs[i]);
+    ga[i] = make_float2(0.f, 0.f);
+    if (vec[i] < NV && ant < A) ga[i] = a.gains[((int64_t)c * P + (YYSET || (P == 2 && PAIR && vec[i] == 1))) * A + ant];
   }
   // a channel's planes of one split are below 2^23 bytes: a uniform base and
   // 32-bit offsets
   const int plane = ap * ap;
   const int64_t vsplit = (int64_t)CovShape<P>::NPROD * plane * sizeof(int2);
   const char* vc = reinterpret_cast<const char*>(a.v) + cl * a.n_split * vsplit;
-  // V of a step: loaded two steps before it is staged
+  // V of a step: loaded two steps before it is staged, with the antennas it is of.
+  // Steps past the range read the antennas that follow (in the table), unused:
+  // every step issues the same loads, which can be counted and waited for alone
   struct Pre {
     int2 v[NE];
-    int b[NB];                          // antennas of the step (-1: none)
+    int ant[NB];
+    float2 gain[NB];                    // b's
   };
   Pre pre0, pre1;
-  int nextb[NB];                        // antennas of the next step to fetch
-  auto lookup = [&](int it) {
+  ConstAnt* next = ants + b0;           // the first antenna of the step fetched next,
+  int nant[NB], nvoff[NB];              // already looked up
+  auto lookup = [&]() {
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
-      const int bi = b0 + NB * it + j;
-      nextb[j] = bi < b1 ? ants[bi].ant : -1;
+      nant[j] = next[j].ant;
+      nvoff[j] = next[j].voff;
     }
+    next += NB;
   };
-  auto fetch = [&](int it, Pre& p) {
-#pragma unroll
-    for (int j = 0; j < NB; ++j) p.b[j] = nextb[j];
+  auto fetch = [&](Pre& p) {
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
-      // always loaded (past the columns or the share: some valid place, unused),
-      // so that the loads in flight can be counted and each set waited for alone
       const int v = vec[i] < NV ? vec[i] : 0;
-      const int b = NB == 1 ? p.b[0] : v ? p.b[NB - 1] : p.b[0];
-      const uint32_t col = __builtin_amdgcn_readfirstlane((P == 2 ? v * plane : 0) + cov_slot(b < 0 ? 0 : b) * ap);
-      const uint32_t off = 8u * (col + sofs[i] + (vec[i] < NV ? tid : 0));
-      p.v[i] = *reinterpret_cast<const int2*>(vc + off);
+      const int pl = P == 1 ? 0 : XY ? 2 : WIDE ? SET : v;
+      const uint32_t col = __builtin_amdgcn_readfirstlane(pl * plane + (v ? nvoff[NB - 1] : nvoff[0]));
+      p.v[i] = *reinterpret_cast<const int2*>(vc + 8u * (col + sofs[i] + (vec[i] < NV ? tid : 0)));
     }
-    lookup(it + 1);
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      // grid 1 of XX | YY is YY's
+      p.ant[j] = nant[j];
+      ConstGain& k = gains[(XY || YYSET || (P == 2 && PAIR && vec[0] == 1) ? A : 0) + nant[j]];
+      p.gain[j] = make_float2(k.x, k.y);
+    }
+    lookup();
   };
-  auto stage = [&](float2* E, const Pre& p) {
+  auto stage = [&](double2* E, const Pre& p) {
 #pragma unroll
     for (int i = 0; i < NE; ++i) {
       const int v = vec[i];
       if (v >= NV) continue;
-      const int b = NB == 1 ? p.b[0] : v ? p.b[NB - 1] : p.b[0];
       const int ant = cov_ant(tid + sofs[i]);
       if (ant >= A) continue;
       int2 val = p.v[i];
-      // the a = b terms are added (or left out) by cov_image_kernel, in float64;
-      // b < 0: the last step of a share at P = 1 may have one antenna only
-      if (b == ant || b < 0) val = make_int2(0, 0);
-      const int ga = P == 2 && v == 1 ? MAXA : 0, go = (P == 2 && v >= 1 ? MAXA : 0) + (b < 0 ? 0 : b);
-      const float2 g = Gl[ga + ant], gb = Gl[go];
-      const float2 h = make_float2(g.x * gb.x + g.y * gb.y, g.y * gb.x - g.x * gb.y);
-      E[v * ESF + ant] = cmul(h, make_float2((float)val.x, (float)val.y));
+      // the a = b terms are added (or left out) by cov_image_kernel
+      if ((v ? p.ant[NB - 1] : p.ant[0]) == ant) val = make_int2(0, 0);
+      const float2 kb = v ? p.gain[NB - 1] : p.gain[0];
+      const double2 g = make_double2(ga[i].x, ga[i].y), k = make_double2(kb.x, kb.y);
+      const double2 h = make_double2(fma(g.x, k.x, g.y * k.y), fma(g.y, k.x, -(g.x * k.y)));
+      const double x = val.x, y = val.y;
+      E[v * ES + tid + sofs[i]] = make_double2(fma(h.x, x, -(h.y * y)), fma(h.x, y, h.y * x));
     }
   };
   // the grids of one step: MASK bit v set: grid v is made
-  auto grid_some = [&](auto mask, const float2* E, float2* M) {
+  auto grid_some = [&](auto mask, const double2* E, double2* M) {
     constexpr int MASK = decltype(mask)::value;
     const char* eb = reinterpret_cast<const char*>(E);
     char* mb = reinterpret_cast<char*>(M);
-    float2 s[NV];
+    double2 s[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) s[v] = make_float2(0.f, 0.f);
+    for (int v = 0; v < NV; ++v) s[v] = make_double2(0.0, 0.0);
     // opaque copies: unpacked here and not, into twice the registers, before
-    // the loop over the share
+    // the loop over the range
     uint32_t n = head.steps, ends = head.ends;
     asm volatile("" : "+s"(n), "+s"(ends));
     int slot = 0;
     auto steps = [&](auto first) {
       constexpr int st = decltype(first)::value * GB;
       if (st >= (int)n) return false;
-      float2 e[GB][NV];                  // a step past the last: a read of E'[0], weight 0
+      double2 e[GB][NV];                 // a step past the last: a read of E'[0], weight 0
 #pragma unroll
       for (int i = 0; i < GB; ++i) {
-        uint32_t ew = prog.e[(st + i) / 2];
-        asm volatile("" : "+v"(ew));
-        const uint32_t off = (st + i) & 1 ? ew >> 16 : ew & 0xFFFFu;
-        const float2* p = reinterpret_cast<const float2*>(eb + off);
+        uint32_t off;
+        if constexpr (UNPACK) {
+          off = eoff[st + i];
+        } else {
+          uint32_t ew = prog.e[(st + i) / 2];
+          asm volatile("" : "+v"(ew));
+          off = i & 1 ? ew >> 16 : ew & 0xFFFFu;
+        }
+        const double2* p = reinterpret_cast<const double2*>(eb + off);
 #pragma unroll
         for (int v = 0; v < NV; ++v)
-          if (MASK >> v & 1) e[i][v] = p[v * ESF];
+          if (MASK >> v & 1) e[i][v] = p[v * ES];
       }
 #pragma unroll
       for (int i = 0; i < GB; ++i) {
-        const float w = prog.w[st + i];
+        const double w = prog.w[st + i];
 #pragma unroll
         for (int v = 0; v < NV; ++v)
           if (MASK >> v & 1) {
-            s[v].x = fmaf(w, e[i][v].x, s[v].x);
-            s[v].y = fmaf(w, e[i][v].y, s[v].y);
+            s[v].x = fma(w, e[i][v].x, s[v].x);
+            s[v].y = fma(w, e[i][v].y, s[v].y);
           }
-        if (ends >> (st + i) & 1) { // uniform over the wave
-          uint32_t cw = slot < 2 ? prog.cell[0] : prog.cell[1];
+        if (S::SLOTS > 1 && (ends >> (st + i) & 1)) { // uniform over the wave
+          uint32_t cw = slot < 2 ? prog.cell[0] : prog.cell[S::SLOTS > 2 ? 1 : 0];
           asm volatile("" : "+v"(cw));
-          float2* cell = reinterpret_cast<float2*>(mb + (slot & 1 ? cw >> 16 : cw & 0xFFFFu));
+          double2* cell = reinterpret_cast<double2*>(mb + (slot & 1 ? cw >> 16 : cw & 0xFFFFu));
           ++slot;
 #pragma unroll
           for (int v = 0; v < NV; ++v)
             if (MASK >> v & 1) {
               cell[v * VS] = s[v];
-              s[v] = make_float2(0.f, 0.f);
+              s[v] = make_double2(0.0, 0.0);
             }
         }
       }
       return true;
     };
-    static_while<kCovSteps / GB>(steps);
+    static_while<S::STEPS / GB>(steps);
+    if (S::SLOTS == 1) {
+      double2* cell = reinterpret_cast<double2*>(mb + prog.cell[0]);
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+        if (MASK >> v & 1) cell[v * VS] = s[v];
+    }
   };
-  int r0 = 0, r1 = 0;                   // first rows of the antennas gridded next
-  auto load_rows = [&](int it) {
-    const int bi = b0 + NB * it;
-    r0 = r1 = ants[bi < b1 ? bi : b0].row;
-    if (NB == 2) r1 = ants[bi + 1 < b1 ? bi + 1 : b0].row;
-  };
-  auto grid = [&](const float2* E, float2* M) {
+  int r0, r1;                           // first rows of the antennas gridded next
+  auto grid = [&](const double2* E, double2* M) {
     if (head.steps == 0) return;
-    const bool need0 = row_hi >= r0 || (WIDE && row_lo <= r0 - 30);
-    const bool need1 = P == 1 ? row_hi >= r1 || (WIDE && row_lo <= r1 - 30)
-                              : row_lo <= r1 + 2 || (WIDE && row_hi >= r1 + 32);
-    constexpr int X = P == 2 ? 4 : 0;
-    if (need0 && need1) grid_some(std::integral_constant<int, 3 | X>{}, E, M);
-    else if (need0) grid_some(std::integral_constant<int, 1 | X>{}, E, M);
-    else if (need1) grid_some(std::integral_constant<int, 2 | X>{}, E, M);
-    else if (X) grid_some(std::integral_constant<int, 4>{}, E, M);
+    // rows that a half plane reads: past b's first (a unit's last row wraps to 31
+    // rows before it, row d = 32 to 30), or up to its last
+    auto up = [&](int r) { return row_hi >= r || (WIDE && row_lo <= r - 30); };
+    auto down = [&](int r) { return row_lo <= r + 2 || (WIDE && row_hi >= r + 32); };
+    constexpr std::integral_constant<int, 1> one{};
+    if constexpr (WIDE) {
+      if (SET == 1 || SET == 3 ? down(r0) : up(r0)) grid_some(one, E, M);
+    } else if constexpr (XY) {
+      grid_some(std::integral_constant<int, 3>{}, E, M);
+    } else {
+      const bool need0 = up(r0), need1 = P == 1 ? up(r1) : down(r1);
+      if (need0 && need1) grid_some(std::integral_constant<int, 3>{}, E, M);
+      else if (need0) grid_some(one, E, M);
+      else if (need1) grid_some(std::integral_constant<int, 2>{}, E, M);
+    }
   };
 
-  // fold: unit u, column ux; group k of the unit covers rows dy0 .. dy0 + 3 of
-  // d of grid vec
+  // fold: unit u, column ux; the unit covers rows dfirst .. dfirst + RU - 1 of d
   const int u = tid / LR, ux = tid % LR;
-  const int hset = u >= S::UNITS / 2 ? 1 : 0, hu = u % (S::UNITS / 2);
-  float2 q[G][3][4];
+  const int hset = PAIR ? __builtin_amdgcn_readfirstlane(u / S::HU) : 0;
+  const int dy0 = RU * (PAIR ? u % S::HU : u);
+  // YY's half plane runs downwards: its units cover d = -(dy0 + RU - 1) .. -dy0
+  const bool down = YYSET || (P == 2 && PAIR && hset);
+  const int dfirst = down ? 1 - RU - dy0 : dy0 + (SET == 3 ? 32 : 0);
+  auto row_of = [&](int d) { return 32 * hset + dy0 + (down ? RU - 1 - d : d); };
+  double2 q[3][RU];
 #pragma unroll
-  for (int k = 0; k < G; ++k)
+  for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-      for (int d = 0; d < 4; ++d) q[k][i][d] = make_float2(0.f, 0.f);
+    for (int d = 0; d < RU; ++d) q[i][d] = make_double2(0.0, 0.0);
   const int ucol = ux < S::W ? ux : S::W;
-  float2* const rout = a.r + (int64_t)logical * S::ROWS * N;
-  auto dy0_of = [&](int k) { return k < S::HG ? 4 * (hu + k * (S::UNITS / 2)) : 4 * (u + (k - S::HG) * S::UNITS); };
-  // grid 1's half plane runs downwards: its group covers d = -(dy0 + 3) .. -dy0
-  auto dfirst_of = [&](int k) { return P == 2 && k < S::HG && hset ? -3 - dy0_of(k) : dy0_of(k); };
-  auto row_of = [&](int k, int d) {
-    return k < S::HG ? 32 * hset + dy0_of(k) + (P == 2 && hset ? 3 - d : d) : 64 + dy0_of(k) + d;
-  };
   int x0 = 0, xfirst = -1;
   // Q_0 one lane on into Q_1; the columns move down
   auto advance = [&]() {
 #pragma unroll
-    for (int k = 0; k < G; ++k)
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        const float2 t = q[k][0][d];
-        float2 sh;
-        if constexpr (LR == N) {         // the lanes are the whole circle of d
-          sh.x = __shfl(t.x, (lane + 63) & 63);
-          sh.y = __shfl(t.y, (lane + 63) & 63);
-        } else {                         // the last column's d has had its last term
-          sh.x = __shfl_up(t.x, 1, LR);
-          sh.y = __shfl_up(t.y, 1, LR);
-          if (ux == 0) sh = make_float2(0.f, 0.f);
-          if (ux == LR - 1) rout[row_of(k, d) * N + ((LR - 1 - x0) & (N - 1))] = t;
-        }
-        q[k][0][d] = make_float2(q[k][1][d].x + sh.x, q[k][1][d].y + sh.y);
-        q[k][1][d] = q[k][2][d];
-        q[k][2][d] = make_float2(0.f, 0.f);
+    for (int d = 0; d < RU; ++d) {
+      const double2 t = q[0][d];
+      double2 sh;
+      if constexpr (LR == N) {           // the lanes are the whole circle of d
+        sh = make_double2(lane_before<0x13C>(t.x), lane_before<0x13C>(t.y));
+      } else {                           // the last column's d has had its last term
+        sh = make_double2(lane_before<0x138>(t.x), lane_before<0x138>(t.y));
+        if (ux == 0) sh = make_double2(0.0, 0.0);
+        if (ux == LR - 1) rout[row_of(d) * N + ((LR - 1 - x0) & (N - 1))] = t;
       }
+      q[0][d] = make_double2(q[1][d].x + sh.x, q[1][d].y + sh.y);
+      q[1][d] = q[2][d];
+      q[2][d] = make_double2(0.0, 0.0);
+    }
     ++x0;
   };
-  auto fold = [&](int it, const float2* M, const CovAnt& b) {
-    if (P == 1 && __builtin_amdgcn_readfirstlane(b0 + 2 * it + hset) >= b1) return;
-    if (xfirst < 0) x0 = xfirst = b.col;
-    while (x0 < b.col) advance();
+  constexpr int NC = XY ? NB : 1;       // antennas a thread folds per step
+  struct Cur {
+    int row, col;
+    double wr[3], wc[3];
+  } held[NC];                           // those of the step gridded now, folded in the next
+  ConstAnt* at = ants + b0;
+  auto load_ant = [&]() {
 #pragma unroll
-    for (int k = 0; k < G; ++k) {
-      const int vec = k < S::HG ? hset : 2;
-      const int s = ((b.row + dfirst_of(k) + S::PADR) & (N - 1)) - S::PADR;
+    for (int j = 0; j < NC; ++j) {
+      ConstAnt& t = at[PAIR && P == 1 ? hset : j];
+      held[j].row = t.row;
+      held[j].col = t.col;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        held[j].wr[i] = t.wr[i];
+        held[j].wc[i] = t.wc[i];
+      }
+    }
+    at += NB;
+  };
+  auto load_rows = [&](ConstAnt* t) {
+    r0 = t[0].row;
+    r1 = t[NB - 1].row;
+  };
+  // the antennas held; left: how many of them exist
+  auto fold = [&](int left, const double2* M) {
+#pragma unroll
+    for (int j = 0; j < NC; ++j) {
+      const int k = PAIR && P == 1 ? hset : j;
+      if (NB == 2 && k >= left) return;
+      const Cur& b = held[j];
+      if (xfirst < 0) x0 = xfirst = b.col;
+      while (x0 < b.col) advance();
+      const double2* Mv = M + (PAIR ? hset : j) * VS + S::PADR * RS + ucol;
+      const int s = ((b.row + dfirst + S::PADR) & (N - 1)) - S::PADR;
       if (s < S::R) {
-        const float2* m = M + vec * VS + (s + S::PADR) * RS + ucol;
-        float2 row[6];
+        double2 z[RU];
 #pragma unroll
-        for (int r = 0; r < 6; ++r) row[r] = m[r * RS];
-        float2 z[4];
+        for (int r = 0; r < RU + 2; ++r) {
+          const double2 m = Mv[(s + r) * RS];
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-          z[d].x = b.wr[0] * row[d].x;
-          z[d].y = b.wr[0] * row[d].y;
-#pragma unroll
-          for (int j = 1; j < 3; ++j) {
-            z[d].x = fmaf(b.wr[j], row[d + j].x, z[d].x);
-            z[d].y = fmaf(b.wr[j], row[d + j].y, z[d].y);
+          for (int d = 0; d < RU; ++d) {
+            if (r == d) z[d] = make_double2(b.wr[0] * m.x, b.wr[0] * m.y);
+            else if (r > d && r - d < 3) {
+              z[d].x = fma(b.wr[r - d], m.x, z[d].x);
+              z[d].y = fma(b.wr[r - d], m.y, z[d].y);
+            }
           }
         }
 #pragma unroll
         for (int i = 0; i < 3; ++i)
 #pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            q[k][i][d].x = fmaf(b.wc[i], z[d].x, q[k][i][d].x);
-            q[k][i][d].y = fmaf(b.wc[i], z[d].y, q[k][i][d].y);
+          for (int d = 0; d < RU; ++d) {
+            q[i][d].x = fma(b.wc[i], z[d].x, q[i][d].x);
+            q[i][d].y = fma(b.wc[i], z[d].y, q[i][d].y);
           }
       }
-      if constexpr (WIDE) {
-        if (k == 0 && hu == 0) {         // i times row d = 32 into row 0
+      if constexpr (WIDE && !XY) {
+        if (dy0 == 0) {                  // i times row d = 32 into row 0
           const int s2 = ((b.row + 32 + S::PADR) & (N - 1)) - S::PADR;
           if (s2 < S::R && s2 >= -2) {
-            const float2* m = M + vec * VS + (s2 + S::PADR) * RS + ucol;
-            float2 z = make_float2(0.f, 0.f);
+            double2 z = make_double2(0.0, 0.0);
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
-              z.x = fmaf(b.wr[j], m[j * RS].x, z.x);
-              z.y = fmaf(b.wr[j], m[j * RS].y, z.y);
+            for (int r = 0; r < 3; ++r) {
+              z.x = fma(b.wr[r], Mv[(s2 + r) * RS].x, z.x);
+              z.y = fma(b.wr[r], Mv[(s2 + r) * RS].y, z.y);
             }
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-              float2& q0 = P == 2 && hset ? q[0][i][3] : q[0][i][0];
-              q0.x = fmaf(-b.wc[i], z.y, q0.x);
-              q0.y = fmaf(b.wc[i], z.x, q0.y);
+              double2& q0 = q[i][YYSET ? RU - 1 : 0];
+              q0.x = fma(-b.wc[i], z.y, q0.x);
+              q0.y = fma(b.wc[i], z.x, q0.y);
             }
           }
         }
@@ -630,59 +680,96 @@ __global__ __launch_bounds__((WIDE ? 1024 : 512), (DENSE && !WIDE ? 2 : 4)) void
     }
   };
 
-  CovAnt cur = {};
-  auto load_ant = [&](int it) {
-    const int bi = P == 2 ? b0 + it : __builtin_amdgcn_readfirstlane(b0 + 2 * it + hset);
-    ConstAnt& t = ants[bi < A ? bi : A - 1];
-    cur.row = t.row;
-    cur.col = t.col;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      cur.wr[i] = t.wr[i];
-      cur.wc[i] = t.wc[i];
-    }
-  };
-  lookup(0);
-  fetch(0, pre0);
-  fetch(1, pre1);
-  if (n_it > 0) {
-    load_ant(0);
-    load_rows(0);
-  }
+  load_rows(at);
+  lookup();
+  fetch(pre0);
+  fetch(pre1);
+  __syncthreads();                      // the last range's last reads done
+  for (int i = tid; i < 2 * (NV * ES + S::MSIZE); i += NT) lds[i] = make_double2(0.0, 0.0);
   __syncthreads();
-  if (n_it > 0) stage(Eb, pre0);
-  fetch(2, pre0);
+  stage(Eb, pre0);
+  fetch(pre0);
   __syncthreads();
-  // step `it`: grid it, stage it + 1 from `p`, fetch it + 3 into it
+  // step `it`: grid it, stage it + 1 from `p`, fetch it + 3 into it, fold it - 1.
+  // Gridding first and ahead of the other waves' folding: LDS and vector ALU
+  // are then wanted by different waves
   auto step = [&](int it, Pre& p) {
-    grid(Eb + (it & 1) * NV * ESF, Mb + (it & 1) * S::MSIZE);
-    load_rows(it + 1);
-    if (it + 1 < n_it) stage(Eb + ((it + 1) & 1) * NV * ESF, p);
-    fetch(it + 3, p);
-    if (it > 0) {                       // the previous antenna's grids, while this one's are made
-      fold(it - 1, Mb + ((it - 1) & 1) * S::MSIZE, cur);
-      load_ant(it);
-    }
+    __builtin_amdgcn_s_setprio(1);
+    grid(Eb + (it & 1) * NV * ES, Mb + (it & 1) * S::MSIZE);
+    __builtin_amdgcn_s_setprio(0);
+    load_rows(at + NB);
+    if (it > 0) fold(NB, Mb + ((it - 1) & 1) * S::MSIZE);   // a step that is not the last is full
+    load_ant();
+    if (it + 1 < n_it) stage(Eb + ((it + 1) & 1) * NV * ES, p);
+    fetch(p);
     __syncthreads();
   };
   for (int it = 0; it < n_it; it += 2) {
     step(it, pre1);
     if (it + 1 < n_it) step(it + 1, pre0);
   }
-  if (n_it > 0) fold(n_it - 1, Mb + ((n_it - 1) & 1) * S::MSIZE, cur);
+  fold(b1 - b0 - NB * (n_it - 1), Mb + ((n_it - 1) & 1) * S::MSIZE);
 
-  // Q_0 and Q_1 into Q_2, then every d the share has touched; zero elsewhere
-  if (xfirst < 0) xfirst = 0;
+  // Q_0 and Q_1 into Q_2, then every d the range has touched; zero elsewhere
+  if (xfirst < 0) x0 = xfirst = 0;      // the second grid of a range of one antenna
   advance();
   advance();
 #pragma unroll
-  for (int k = 0; k < G; ++k)
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      float2* o = rout + row_of(k, d) * N;
-      o[(ux - x0) & (N - 1)] = q[k][0][d];
-      if (LR < N && ux < LR - (x0 - xfirst)) o[(LR - xfirst + ux) & (N - 1)] = make_float2(0.f, 0.f);
+  for (int d = 0; d < RU; ++d) {
+    double2* o = rout + row_of(d) * N;
+    o[(ux - x0) & (N - 1)] = q[0][d];
+    if (LR < N && ux < LR - (x0 - xfirst)) o[(LR - xfirst + ux) & (N - 1)] = make_double2(0.0, 0.0);
+  }
+}
+
+// A channel costs A passes of a grid per product, whatever T is, in float64
+// throughout: R is summed before the transform, so that its rounding spreads over
+// every pixel alike, and a pixel far below the peak would lose what a sum of
+// squares keeps (in float32, 3e-9 of the largest possible pixel: up to 4 % of
+// pixels 50 dB below a point source's peak, and negative power).
+// A workgroup takes the antennas b of its range in column order.  Per b:
+// E'[a] = g_a conj(g_b) V_ab is staged, gridded with the channel's program
+// (held in registers for the whole range), and folded into R: a thread owns
+// one aperture column and two rows of d, forms the row taps of M_b at its rows,
+// and adds them, times the three column taps, to its sums Q_0 .. Q_2 of the
+// aperture columns col .. col + 2.  When the next antenna starts at the next
+// column, Q_0 moves one lane on into Q_1 (the same d), so a sum stays in
+// registers until its last term and R is written once.
+// Bound: the chain of a step (an antenna's gridding, staging and folding between
+// two barriers; vector ALU 30 %, LDS 40 % of the cycles).  132 channels of 256
+// dual-pol antennas: 228 us, the wide block's 461 (the direct kernels take 1173 at
+// T = 1000 and 1752 at T = 1250).  On the way, at 128 channels: whole rows per
+// wave instead of bands 260 against 244 us (wide 587 and 515); gridding at a raised
+// priority 240 (469), as LDS and vector ALU are then wanted by different waves;
+// antennas' table read by counted pointers, one step ahead, 224 (436); four
+// steps' reads in flight instead of two 250, longest slots' waves relieved of
+// staging and of the fold's busiest rows 244.  512 threads with four rows of d
+// each spill (106 registers).
+template <int P, bool WIDE, int KIND>
+__global__ __launch_bounds__(1024) void cov_fold_kernel(CovFoldArgs a) {
+  using S = CovFold<P, WIDE, KIND>;
+  __shared__ __align__(16) double2 lds[2 * (S::NV * S::ES + S::MSIZE)];
+  const int w = wg_range_index(blockIdx.x, a.W, 1);
+  int64_t u = w * a.units / a.W;
+  const int64_t u1 = (w + 1) * a.units / a.W;
+  while (u < u1) {
+    const int cg = (int)(u / a.n_ant), b0 = (int)(u % a.n_ant);
+    const int b1 = (int)(b0 + (u1 - u) < a.n_ant ? b0 + (u1 - u) : a.n_ant);
+    double2* r = a.r + (int64_t)(w + cg) * S::ROWS * S::N;
+    if constexpr (P == 1) {
+      cov_fold_body<P, 0, WIDE, KIND>(a, lds, r, cg, b0, b1);
+    } else if constexpr (!WIDE) {
+      cov_fold_body<P, 0, WIDE, KIND>(a, lds, r, cg, b0, b1);
+      cov_fold_body<P, 1, WIDE, KIND>(a, lds, r + S::SROWS * S::N, cg, b0, b1);
+    } else if (cg % 2 == 0) {
+      cov_fold_body<P, 0, WIDE, KIND>(a, lds, r, cg / 2, b0, b1);
+      cov_fold_body<P, 2, WIDE, KIND>(a, lds, r + S::SROWS * S::N, cg / 2, b0, b1);
+    } else {
+      cov_fold_body<P, 1, WIDE, KIND>(a, lds, r, cg / 2, b0, b1);
+      cov_fold_body<P, 3, WIDE, KIND>(a, lds, r + S::SROWS * S::N, cg / 2, b0, b1);
     }
+    u += b1 - b0;
+  }
 }
 
 // 8-point transform, positive exponent, float64.
@@ -732,27 +819,29 @@ __device__ __forceinline__ void lines64_f64(double2* p, int ls, int ps, const do
 }
 
 struct CovImageArgs {
-  const float2* r;          // [channel - c0][chunk][rows][64]
-  const int2* v;            // cov_corr_kernel's output
+  const double2* r;         // cov_fold_kernel's output
+  const int2* v;            // cov_corr_kernel's output, the splits added
   const float2* gains;      // [C][P][A]
   const CovAnt* ants;       // [C][A]
   double2* image;           // [C][4 or 1][64][64]
   int n_ant, ap;
-  int c0, n_split, n_chunk, reset, transposed;
+  int c0, n_split, reset, transposed;
+  int W;                    // the fold's workgroups and units
+  int64_t units;
+  int wide;                 // layout of r: CovFold<P, wide, ..>
   int autos;                // 1: leave the a = b terms out
 };
 
-// One workgroup per product (XX, XY, YY) of a channel: the shares summed in
-// share order, the a = b terms added, the plane transformed in float64 and the
-// image written (fftshifted).  XX and YY stay apart (as the parts of one complex
-// plane, the rounding of the one would show in the other).  The a = b terms, sum_a g_P conj(g_Q) V_aa (w_a autocorrelated),
-// are by far the largest values of R, at its 25 innermost offsets: summed here
-// in float64 rather than with the others in float32, they cost the image no
-// accuracy (without this the error at 256 antennas, T = 1000, against 64 bits
-// was three times larger).  Bound: latency (one pass over the shares).
+// One workgroup per product (XX, XY, YY) of a channel: the ranges' slots summed in
+// order, the a = b terms added, the plane transformed in float64 and the image
+// written (fftshifted).  XX and YY stay apart (as the parts of one complex
+// plane, the rounding of the one would show in the other).  The a = b terms,
+// sum_a g_P conj(g_Q) V_aa (w_a autocorrelated), at R's 25 innermost offsets, are
+// added here, so that leaving them out costs nothing.  Bound: latency (one pass
+// over the slots).
 template <int P>
 __global__ __launch_bounds__(512) void cov_image_kernel(CovImageArgs a) {
-  constexpr int N = 64, LS = N + 1, ROWS = CovFold<P, false, false>::ROWS, NPL = P == 2 ? 3 : 1;
+  constexpr int N = 64, LS = N + 1, NPL = P == 2 ? 3 : 1;
   __shared__ double2 pl[N * LS];
   __shared__ double2 w64[N];
   __shared__ double2 asum[8][9];
@@ -763,20 +852,26 @@ __global__ __launch_bounds__(512) void cov_image_kernel(CovImageArgs a) {
     sincospi(tid / 32.0, &s, &co);
     w64[tid] = make_double2(co, s);
   }
-  const float2* r = a.r + (int64_t)cl * a.n_chunk * ROWS * N;
-  // NB sums over the shares at once, so that their loads are in flight together
-  auto sums = [&](auto count, auto at, auto& out) {
+  const int groups = a.wide ? CovFold<P, true, kCovPlain>::GROUPS : CovFold<P, false, kCovPlain>::GROUPS;
+  const int rows = a.wide ? CovFold<P, true, kCovPlain>::ROWS : CovFold<P, false, kCovPlain>::ROWS;   // of a slot
+  // NB sums over the slots of the channel's group g at once, so that their loads
+  // are in flight together
+  auto sums = [&](auto count, int g, auto at, auto* out) {
     constexpr int NB = decltype(count)::value;
+    const int cg = cl * groups + g;
+    const int w0 = cov_owner((int64_t)cg * a.n_ant, a.units, a.W);
+    const int w1 = cov_owner((int64_t)(cg + 1) * a.n_ant - 1, a.units, a.W);
+    const double2* r = a.r + (int64_t)(w0 + cg) * rows * N;
     int off[NB];
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
       off[j] = at(j);
       out[j] = make_double2(0.0, 0.0);
     }
-    for (int k = 0; k < a.n_chunk; ++k) {
-      float2 v[NB];
+    for (int k = w0; k <= w1; ++k, r += rows * N) {
+      double2 v[NB];
 #pragma unroll
-      for (int j = 0; j < NB; ++j) v[j] = r[(int64_t)k * ROWS * N + off[j]];
+      for (int j = 0; j < NB; ++j) v[j] = r[off[j]];
 #pragma unroll
       for (int j = 0; j < NB; ++j) {
         out[j].x += v[j].x;
@@ -804,8 +899,8 @@ __global__ __launch_bounds__(512) void cov_image_kernel(CovImageArgs a) {
         ry[d] = rx[d] = 0.0;
 #pragma unroll
         for (int j = 0; j + d < 3; ++j) {
-          ry[d] += (double)w.wr[j] * w.wr[j + d];
-          rx[d] += (double)w.wc[j] * w.wc[j + d];
+          ry[d] += w.wr[j] * w.wr[j + d];
+          rx[d] += w.wc[j] * w.wc[j + d];
         }
       }
 #pragma unroll
@@ -827,7 +922,12 @@ __global__ __launch_bounds__(512) void cov_image_kernel(CovImageArgs a) {
   }
   if (plane == 1) {
     double2 x[8];
-    sums(std::integral_constant<int, 8>{}, [&](int j) { return 64 * N + tid + 512 * j; }, x);
+    if (a.wide) {                      // a half in either group
+      sums(std::integral_constant<int, 4>{}, 0, [&](int j) { return 32 * N + tid + 512 * j; }, x);
+      sums(std::integral_constant<int, 4>{}, 1, [&](int j) { return 32 * N + tid + 512 * j; }, x + 4);
+    } else {
+      sums(std::integral_constant<int, 8>{}, 0, [&](int j) { return 64 * N + tid + 512 * j; }, x);
+    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const int i = tid + 512 * j;
@@ -835,21 +935,22 @@ __global__ __launch_bounds__(512) void cov_image_kernel(CovImageArgs a) {
     }
   } else {
     // the upper half plane of XX or YY (held for -d: YY(-d) = conj YY(d)); at
-    // P = 1 two shares of XX
-    const int row0 = plane == 2 ? 32 : 0;
+    // P = 1, half the grid, two parts of XX
+    const int g = plane == 2 && a.wide ? 1 : 0, row0 = plane == 2 && !a.wide ? 32 : 0;
     const double sign = plane == 2 ? -1.0 : 1.0;
     constexpr int H = P == 1 ? 8 : 4;
+    const bool two = P == 1 && !a.wide;
     double2 x[H];
-    sums(std::integral_constant<int, H>{},
+    sums(std::integral_constant<int, H>{}, g,
          [&](int j) {
            const int i = tid + 512 * (j & 3), dy = i >> 6, dx = i & 63;
-           return (row0 + (j >> 2) * 32 + dy) * N + (plane == 2 ? (N - dx) & (N - 1) : dx);
+           return (row0 + (two ? (j >> 2) * 32 : 0) + dy) * N + (plane == 2 ? (N - dx) & (N - 1) : dx);
          },
          x);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const int i = tid + 512 * j, dy = i >> 6, dx = i & 63, mx = (N - dx) & (N - 1);
-      if (P == 1) x[j] = make_double2(x[j].x + x[H - 4 + j].x, x[j].y + x[H - 4 + j].y);
+      if (two) x[j] = make_double2(x[j].x + x[H - 4 + j].x, x[j].y + x[H - 4 + j].y);
       if (dy) {
         pl[dy * LS + dx] = make_double2(x[j].x, sign * x[j].y);
         pl[(N - dy) * LS + mx] = make_double2(x[j].x, -sign * x[j].y);
@@ -859,10 +960,10 @@ __global__ __launch_bounds__(512) void cov_image_kernel(CovImageArgs a) {
       // rows 0 and 32: S(d) = R_0(d) + i R_32(d), each Hermitian in d
       const int dx = tid, mx = (N - dx) & (N - 1);
       double2 s[4];
-      sums(std::integral_constant<int, 4>{},
-           [&](int j) { return (row0 + (j >= 2 ? 32 : 0) * (P == 1)) * N + (j & 1 ? mx : dx); }, s);
+      sums(std::integral_constant<int, 4>{}, g,
+           [&](int j) { return (row0 + (two && j >= 2 ? 32 : 0)) * N + (j & 1 ? mx : dx); }, s);
       double2 p = s[0], m = s[1];
-      if (P == 1) {
+      if (two) {
         p = make_double2(p.x + s[2].x, p.y + s[2].y);
         m = make_double2(m.x + s[3].x, m.y + s[3].y);
       }
@@ -902,7 +1003,8 @@ __global__ __launch_bounds__(512) void cov_image_kernel(CovImageArgs a) {
       put(1, z);
       put(2, make_double2(z.x, -z.y));
     } else {
-      put(plane == 2 ? 3 : 0, make_double2(z.x, 0.0));
+      // a sum of squares less its rounding: never below zero (NaN stays NaN)
+      put(plane == 2 ? 3 : 0, make_double2(a.autos || !(z.x <= 0.0) ? z.x : 0.0, 0.0));
     }
   }
 }

@@ -6,11 +6,11 @@
 namespace epic {
 namespace covar {
 
-// Shape of a launch: polarisations, wide block, the fold's variant for many
-// antennas or crowded cells.
+// Shape of a launch: polarisations, wide block, kind of fold (kCovPlain, ..).
 struct Shape {
   int n_pol;
-  bool wide, dense;
+  bool wide;
+  int kind;
 };
 
 int fold_blocks_per_cu(const Shape& s);

@@ -62,7 +62,7 @@ struct Geometry {
   std::vector<int> tcell;             // [C][A][KK] the same taps translated to start at (0, 0)
   std::vector<float> w;               // [C][A][KK] (real parts for complex kernels)
   std::vector<float> wi;              // [C][A][KK] imaginary parts, empty for real kernels
-  std::vector<float> wj, wx;          // [C][A][K] the Gaussian's row and column factors (w = wj wx)
+  std::vector<double> wj, wx;         // [C][A][K] the Gaussian's row and column factors (w = wj wx)
   bool fits_half = true;              // every channel's taps fit an N/2 x N/2 block
   bool fits_wide = true;              // ... a 3N/4 x 3N/4 block (the wide fused variant,
                                       // whose rows orient_wide then trims)
@@ -183,9 +183,9 @@ struct epic_ctx {
   // covariance form of long integrations (covar.hpp)
   bool cov_allowed = true;            // false for the blocks of a batch
   bool cov = false;                   // the current geometry can take it
-  bool cov_dense = false;             // ... with the fold's variant for many antennas or crowded cells
+  int cov_kind = epic::kCovPlain;     // ... with this kind of fold
   int cov_ap = 0;                     // antennas rounded up to the tile
-  int cov_chunks = 1;                 // shares of a channel's antennas in the fold
+  int cov_fold_w = 1;                 // the fold's resident workgroups
   int cov_chan = 0;                   // channels per pass the workspace holds (one split each)
   int cov_gchunks = 1, cov_ggroups = 1;   // shares of b in the gradient: workgroups, and per workgroup
   DevMem cov_ants, cov_v, cov_r, cov_head, cov_prog, cov_hat, cov_gpart;
@@ -306,8 +306,8 @@ epic_status build_geometry(const epic_config& cfg, const double* xy, const doubl
       if (!std::isfinite(kernels[o])) { m = "kernel value is not finite"; return EPIC_E_INVALID; }
   }
   const int K1 = kernels ? 0 : K;
-  g.wj.assign((size_t)C * A * K1, 0.f);
-  g.wx.assign((size_t)C * A * K1, 0.f);
+  g.wj.assign((size_t)C * A * K1, 0.0);
+  g.wx.assign((size_t)C * A * K1, 0.0);
   g.fits_half = true;
   g.fits_wide = true;
   g.ext_j = g.ext_i = 0;
@@ -329,8 +329,8 @@ epic_status build_geometry(const epic_config& cfg, const double* xy, const doubl
       }
       for (int d = 0; d < K1; ++d) {
         const double di = i0 - h + d - X, dj = j0 - h + d - Y;
-        g.wj[((size_t)c * A + a) * K + d] = (float)std::exp(-dj * dj * inv2s2);
-        g.wx[((size_t)c * A + a) * K + d] = (float)std::exp(-di * di * inv2s2);
+        g.wj[((size_t)c * A + a) * K + d] = std::exp(-dj * dj * inv2s2);
+        g.wx[((size_t)c * A + a) * K + d] = std::exp(-di * di * inv2s2);
       }
       int k = 0;
       for (int dj = -h; dj <= h; ++dj)
@@ -1441,150 +1441,208 @@ FusedGrid fused_grid(const epic_ctx* x, int64_t n_time, int max_team = kMaxTeam)
 
 constexpr int kCovMaxParts = 4;                       // time splits per channel at most
 
-epic::covar::Shape cov_shape(const epic_ctx* x) { return {x->cfg.n_pol, x->wide, x->cov_dense}; }
+epic::covar::Shape cov_shape(const epic_ctx* x) { return {x->cfg.n_pol, x->wide, x->cov_kind}; }
+
+// Groups of sets of a channel in the fold (CovFold), and rows of a slot.
+int cov_groups(const epic_ctx* x) { return x->wide && x->cfg.n_pol == 2 ? epic::CovFold<2, true, epic::kCovPlain>::GROUPS : 1; }
+int cov_slot_rows(const epic_ctx* x) {
+  if (x->wide) return x->cfg.n_pol == 2 ? epic::CovFold<2, true, epic::kCovPlain>::ROWS : epic::CovFold<1, true, epic::kCovPlain>::ROWS;
+  return x->cfg.n_pol == 2 ? epic::CovFold<2, false, epic::kCovPlain>::ROWS : epic::CovFold<1, false, epic::kCovPlain>::ROWS;
+}
+// Workgroups of the fold for nc channels: one per resident place, but at least
+// four antennas each (a range costs its antennas and about four more: program,
+// first stage, output) and at most 32 slots a channel group for the image to add.
+int cov_fold_wgs(const epic_ctx* x, int nc) {
+  const int64_t cg = (int64_t)nc * cov_groups(x);
+  return (int)std::max<int64_t>(1, std::min({(int64_t)x->cov_fold_w, cg * x->cfg.n_ant / 4, cg * 32}));
+}
 
 constexpr size_t kCovWorkspace = (size_t)384 << 20;   // bytes of covariances at most
 
 size_t cov_v_bytes(const epic_ctx* x) {               // one channel, one split
   return (size_t)(x->cfg.n_pol == 2 ? 3 : 1) * x->cov_ap * x->cov_ap * sizeof(int2);
 }
-size_t cov_r_bytes(const epic_ctx* x) {               // one channel
-  return (size_t)x->cov_chunks * (x->cfg.n_pol == 2 ? 128 : 64) * 64 * sizeof(float2);
+size_t cov_r_bytes(const epic_ctx* x, int nc) {       // of a pass
+  return ((size_t)x->cov_fold_w + (size_t)nc * cov_groups(x)) * cov_slot_rows(x) * 64 * sizeof(double2);
 }
 
-// The fold's gridding programs (CovProgHead): each wave grids consecutive
-// aperture rows, cut so that the longest wave has as few steps as can be.  A
-// wave's cells go to slots of 64 by number of entries, most first; within a
-// slot lanes follow the cells' columns, so that neighbouring lanes read common
-// antennas.  The entries of a cell are taken in the order that, step by step,
-// loads the LDS banks of each 16 lanes least.  false: an aperture so crowded
-// that a wave needs more than S::STEPS steps or kCovSlots slots.
-template <typename S>
-bool build_cov_programs(const Geometry& g, std::vector<epic::CovProgHead>& heads, std::vector<uint32_t>& words) {
-  constexpr int N = 64, NW = S::NW, kSteps = S::STEPS;
-  using Lane = epic::CovProgLane<S::STEPS>;
-  const int C = g.C, A = g.A, KK = g.KK;
-  const int rows = g.wide_rows ? g.wide_rows : S::R, cols = S::W, rs = S::RS, padr = S::PADR;
-  heads.assign((size_t)C * NW, epic::CovProgHead{});
-  std::vector<Lane> prog((size_t)C * NW * 64, Lane{});
+// The fold's gridding program of one channel (CovProgHead).  The aperture's rows
+// are cut into four bands of consecutive rows, each gridded by a quarter of the
+// waves.  A band's cells go to slots of 64 by number of entries, most first, so
+// that a slot's lanes end together, and the slots to the band's waves, longest
+// first to the least loaded; the cut is the one with the least sum over bands of
+// steps squared.  (Whole rows per wave, cut to the same longest wave, cost a
+// quarter more steps: every wave that holds a crowded cell runs all of its lanes
+// to that cell's end.)  Within a slot lanes follow the cells' columns, so that
+// neighbouring lanes read common antennas.  The entries of a cell are taken in
+// the order that, step by step, loads the LDS banks of each 16 lanes least.
+// false: an aperture so crowded that a wave needs more than S::STEPS steps or
+// S::SLOTS slots.
+template <typename S> struct CovProgramBuilder {
+  using Lane = epic::CovProgLane<S::STEPS, S::SLOTS>;
+  static constexpr int N = 64, NW = S::NW, K = 3, kBands = 4, kPerBand = NW / kBands, kSteps = S::STEPS;
+  static constexpr int kZero = S::MAXA;                // first of the 16 zero slots of E'
   struct Entry {
-    int ant;
-    float w;
+    int ant;                                           // place in E'
+    double w;
   };
-  std::vector<std::vector<Entry>> cells((size_t)rows * cols);
-  Entry left[64][kSteps];
-  int nleft[64];
-  std::vector<uint32_t> seen(A + 16, 0u);
+  using Count = std::array<int, kSteps + 1>;           // cells by entries
+  const Geometry& g;
+  const int rows, cols = S::W;
+  std::vector<std::vector<Entry>> cells;
+  std::vector<Count> count;                            // of the rows above each row
+  std::vector<uint32_t> seen;
   uint32_t stamp = 0;
-  // cells by entries, per row; the steps of a wave that grids rows of summed
-  // counts n: per slot its largest cell
-  using Count = std::array<int, kSteps + 1>;
-  std::vector<Count> count(rows);
-  auto fits = [&](const Count& n, int bound) {
-    int steps = 0, slots = 0, room = 0;
+
+  explicit CovProgramBuilder(const Geometry& geom)
+      : g(geom), rows(geom.wide_rows ? geom.wide_rows : S::R), cells((size_t)rows * cols), count(rows + 1),
+        seen(kZero + 16, 0u) {}
+
+  // steps of the slots of rows [i, j), longest first; their number
+  int slot_steps(int i, int j, int (&out)[kPerBand * S::SLOTS + 1]) const {
+    int slots = 0, room = 0;
     for (int e = kSteps; e > 0; --e)
-      for (int k = n[e] - room; ; k -= 64) {
+      for (int k = count[j][e] - count[i][e] - room;; k -= 64) {
         if (k <= 0) {
           room = -k;
           break;
         }
-        steps += e;
-        ++slots;
+        if (slots > kPerBand * S::SLOTS) return slots;
+        out[slots++] = e;
       }
-    return steps <= bound && slots <= epic::kCovSlots;
-  };
-  for (int c = 0; c < C; ++c) {
+    return slots;
+  }
+
+  bool channel(int c, epic::CovProgHead* heads, Lane* lanes) {
     for (auto& v : cells) v.clear();
-    for (int a = 0; a < A; ++a)
-      for (int k = 0; k < KK; ++k) {
-        const size_t o = ((size_t)c * A + a) * KK + k;
-        cells[(size_t)(g.tcell[o] / N) * cols + g.tcell[o] % N].push_back({a, g.w[o]});
+    for (int a = 0; a < g.A; ++a)
+      for (int k = 0; k < g.KK; ++k) {
+        const size_t o = ((size_t)c * g.A + a) * g.KK + k, f = ((size_t)c * g.A + a) * K;
+        cells[(size_t)(g.tcell[o] / N) * cols + g.tcell[o] % N].push_back(
+            {epic::cov_slot(a), g.wj[f + k / K] * g.wx[f + k % K]});
       }
-    int most = 1;
+    count[0].fill(0);
     for (int j = 0; j < rows; ++j) {
-      count[j].fill(0);
+      count[j + 1] = count[j];
       for (int i = j * cols; i < (j + 1) * cols; ++i) {
         const int n = (int)cells[i].size();
         if (n > kSteps) return false;
-        ++count[j][n];
-        most = std::max(most, n);
+        ++count[j + 1][n];
       }
     }
-    // the least bound on a wave's steps under which the rows fit the waves
-    int cut[NW + 1] = {0};
-    for (int bound = most;; ++bound) {
-      if (bound > kSteps) return false;
-      int j = 0;
-      for (int w = 0; w < NW; ++w) {
-        Count n{};
-        for (; j < rows; ++j) {
-          Count m = n;
-          for (int e = 1; e <= kSteps; ++e) m[e] += count[j][e];
-          if (!fits(m, bound)) break;
-          n = m;
+    // the cut: cost[k][j] of the first j rows in k + 1 bands
+    constexpr int kNone = INT32_MAX;
+    std::array<std::vector<int>, kBands> cost, from;
+    int steps[kPerBand * S::SLOTS + 1];
+    for (int k = 0; k < kBands; ++k) {
+      cost[k].assign(rows + 1, kNone);
+      from[k].assign(rows + 1, 0);
+      for (int j = 0; j <= rows; ++j)
+        for (int i = 0; i <= (k ? j : 0); ++i) {
+          if (k && cost[k - 1][i] == kNone) continue;
+          const int n = slot_steps(i, j, steps);
+          if (n > kPerBand * S::SLOTS) continue;
+          int t = 0;
+          for (int s = 0; s < n; ++s) t += steps[s];
+          const int v = (k ? cost[k - 1][i] : 0) + t * t;
+          if (v < cost[k][j]) {
+            cost[k][j] = v;
+            from[k][j] = i;
+          }
         }
-        cut[w + 1] = j;
-      }
-      if (j == rows) break;
     }
-    for (int w = 0; w < NW; ++w) {
-      epic::CovProgHead& h = heads[(size_t)c * NW + w];
-      Lane* out = &prog[((size_t)c * NW + w) * 64];
-      h.row_lo = cut[w];
-      h.row_hi = cut[w + 1] - 1;
+    if (cost[kBands - 1][rows] == kNone) return false;
+    int cut[kBands + 1];
+    cut[kBands] = rows;
+    for (int k = kBands - 1; k >= 0; --k) cut[k] = from[k][cut[k + 1]];
+    for (int k = 0; k < kBands; ++k) {
       std::vector<int> list;
-      for (int i = cut[w] * cols; i < cut[w + 1] * cols; ++i)
+      for (int i = cut[k] * cols; i < cut[k + 1] * cols; ++i)
         if (!cells[i].empty()) list.push_back(i);
       std::stable_sort(list.begin(), list.end(), [&](int p, int q) { return cells[p].size() > cells[q].size(); });
+      int load[kPerBand] = {0}, held[kPerBand] = {0};
       for (size_t s0 = 0; s0 < list.size(); s0 += 64) {
+        int r = -1;
+        for (int w = 0; w < kPerBand; ++w)
+          if (held[w] < S::SLOTS && (r < 0 || load[w] < load[r])) r = w;
         std::vector<int> slot(list.begin() + s0, list.begin() + std::min(list.size(), s0 + 64));
-        const int n = (int)cells[slot[0]].size(), k = (int)(s0 / 64);
-        std::stable_sort(slot.begin(), slot.end(), [&](int p, int q) {
-          return p % cols != q % cols ? p % cols < q % cols : p < q;
-        });
-        // the lanes' entries not yet taken: left[l][0 .. nleft[l])
-        for (int l = 0; l < 64; ++l) {
-          // lanes past the wave's last cell store zeros to a padding column
-          int cell = padr * rs + cols;
-          nleft[l] = 0;
-          if (l < (int)slot.size()) {
-            for (const Entry& e : cells[slot[l]]) left[l][nleft[l]++] = e;
-            cell = (padr + slot[l] / cols) * rs + slot[l] % cols;
-          }
-          out[l].cell[k / 2] |= (uint32_t)(cell * 8) << (16 * (k % 2));
-        }
-        for (int st = 0; st < n; ++st, ++h.steps)
-          for (int q = 0; q < 4; ++q) {
-            int used[16] = {0};
-            ++stamp;                                     // seen[a] == stamp: read by this step's 16 lanes
-            for (int l = 16 * q; l < 16 * q + 16; ++l) {
-              auto cost = [&](int ant) { return seen[ant] == stamp ? -1 : used[ant % 16]; };
-              int ant, best = 0;
-              float wt = 0.f;
-              for (int e = 1; e < nleft[l]; ++e)
-                if (cost(left[l][e].ant) < cost(left[l][best].ant)) best = e;
-              // a lane with fewer entries than steps left may wait on a zero slot
-              if (nleft[l] && (nleft[l] >= n - st || cost(left[l][best].ant) <= 0)) {
-                ant = left[l][best].ant;
-                wt = left[l][best].w;
-                left[l][best] = left[l][--nleft[l]];
-              } else {
-                ant = A;
-                for (int e = 1; e < 16; ++e)
-                  if (cost(A + e) < cost(ant)) ant = A + e;
-              }
-              if (seen[ant] != stamp) {
-                ++used[ant % 16];
-                seen[ant] = stamp;
-              }
-              out[l].e[h.steps / 2] |= (uint32_t)(ant * 8) << (16 * (h.steps % 2));
-              out[l].w[h.steps] = wt;
-            }
-          }
-        h.ends |= 1u << (h.steps - 1);
+        const int n = (int)cells[slot[0]].size();
+        if (r < 0 || load[r] + n > kSteps) return false;
+        // waves w, w + 4, .. share a SIMD: one of each band's ranks on each
+        const int wave = kPerBand * k + (r + k) % kPerBand;
+        add_slot(heads[wave], lanes + 64 * wave, slot, held[r]++, n);
+        load[r] += n;
       }
     }
+    return true;
   }
+
+  void add_slot(epic::CovProgHead& h, Lane* out, std::vector<int>& slot, int k, int n) {
+    const int lo = *std::min_element(slot.begin(), slot.end()) / cols;
+    const int hi = *std::max_element(slot.begin(), slot.end()) / cols;
+    h.row_lo = k ? std::min<uint32_t>(h.row_lo, lo) : lo;
+    h.row_hi = k ? std::max<uint32_t>(h.row_hi, hi) : hi;
+    std::stable_sort(slot.begin(), slot.end(), [&](int p, int q) {
+      return p % cols != q % cols ? p % cols < q % cols : p < q;
+    });
+    // the lanes' entries not yet taken: left[l][0 .. nleft[l])
+    Entry left[64][kSteps];
+    int nleft[64];
+    for (int l = 0; l < 64; ++l) {
+      // lanes past the slot's last cell store zeros to a padding column
+      int cell = S::PADR * S::RS + cols;
+      nleft[l] = 0;
+      if (l < (int)slot.size()) {
+        for (const Entry& e : cells[slot[l]]) left[l][nleft[l]++] = e;
+        cell = (S::PADR + slot[l] / cols) * S::RS + slot[l] % cols;
+      }
+      out[l].cell[k / 2] |= (uint32_t)(cell * sizeof(double2)) << (16 * (k % 2));
+    }
+    for (int st = 0; st < n; ++st, ++h.steps)
+      for (int q = 0; q < 4; ++q) {
+        int used[16] = {0};
+        ++stamp;                                       // seen[a] == stamp: read by this step's 16 lanes
+        for (int l = 16 * q; l < 16 * q + 16; ++l) {
+          auto cost = [&](int ant) { return seen[ant] == stamp ? -1 : used[ant % 16]; };
+          int ant, best = 0;
+          double wt = 0.0;
+          for (int e = 1; e < nleft[l]; ++e)
+            if (cost(left[l][e].ant) < cost(left[l][best].ant)) best = e;
+          // a lane with fewer entries than steps left may wait on a zero slot
+          if (nleft[l] && (nleft[l] >= n - st || cost(left[l][best].ant) <= 0)) {
+            ant = left[l][best].ant;
+            wt = left[l][best].w;
+            left[l][best] = left[l][--nleft[l]];
+          } else {
+            ant = kZero;
+            for (int e = 1; e < 16; ++e)
+              if (cost(kZero + e) < cost(ant)) ant = kZero + e;
+          }
+          if (seen[ant] != stamp) {
+            ++used[ant % 16];
+            seen[ant] = stamp;
+          }
+          uint32_t& e = out[l].e[h.steps / 2];
+          const int shift = 16 * (h.steps % 2);
+          e = (e & ~(0xFFFFu << shift)) | (uint32_t)(ant * sizeof(double2)) << shift;
+          out[l].w[h.steps] = wt;
+        }
+      }
+    h.ends |= 1u << (h.steps - 1);
+  }
+};
+
+template <typename S>
+bool build_cov_programs(const Geometry& g, std::vector<epic::CovProgHead>& heads, std::vector<uint32_t>& words) {
+  using Builder = CovProgramBuilder<S>;
+  using Lane = typename Builder::Lane;
+  heads.assign((size_t)g.C * S::NW, epic::CovProgHead{});
+  Lane idle{};                                         // steps past a wave's last read a zero slot
+  for (uint32_t& e : idle.e) e = 0x10001u * (uint32_t)(Builder::kZero * sizeof(double2));
+  std::vector<Lane> prog((size_t)g.C * S::NW * 64, idle);
+  Builder b(g);
+  for (int c = 0; c < g.C; ++c)
+    if (!b.channel(c, &heads[(size_t)c * S::NW], &prog[(size_t)c * S::NW * 64])) return false;
   words.resize(prog.size() * sizeof(Lane) / 4);
   std::memcpy(words.data(), prog.data(), words.size() * 4);
   return true;
@@ -1593,10 +1651,11 @@ bool build_cov_programs(const Geometry& g, std::vector<epic::CovProgHead>& heads
 // Tables and workspace of the covariance form for the current geometry; the
 // context runs without it if they cannot be had.
 void build_cov(epic_ctx* x, const Geometry& g) {
-  const int C = x->cfg.n_chan, A = x->cfg.n_ant, N = x->cfg.grid_n, K = x->cfg.kernel_support;
+  const int C = x->cfg.n_chan, A = x->cfg.n_ant, N = x->cfg.grid_n, K = x->cfg.kernel_support, P = x->cfg.n_pol;
   x->cov = false;
   if (!x->cov_allowed || !x->fused || N != 64 || K != 3 || x->cpx || A > 512) return;
-  std::vector<epic::CovAnt> ants((size_t)C * A);
+  x->cov_ap = (A + epic::kCovTile - 1) / epic::kCovTile * epic::kCovTile;
+  std::vector<epic::CovAnt> ants((size_t)C * A + epic::kCovAntsPast, epic::CovAnt{});
   std::vector<int> order(A);
   for (int c = 0; c < C; ++c) {
     const int* cell = &g.tcell[(size_t)c * A * g.KK];
@@ -1608,38 +1667,35 @@ void build_cov(epic_ctx* x, const Geometry& g) {
       const size_t o = (size_t)c * A + order[i];
       t = epic::CovAnt{};
       t.ant = order[i];
+      t.voff = epic::cov_slot(order[i]) * x->cov_ap;
       t.row = g.tcell[o * g.KK] / N;
       t.col = g.tcell[o * g.KK] % N;
       for (int d = 0; d < K; ++d) {
         t.wr[d] = (x->transposed ? g.wx : g.wj)[o * K + d];
         t.wc[d] = (x->transposed ? g.wj : g.wx)[o * K + d];
+        t.fr[d] = (float)t.wr[d];
+        t.fc[d] = (float)t.wc[d];
       }
     }
   }
   std::vector<epic::CovProgHead> heads;
   std::vector<uint32_t> prog;
-  x->cov_dense = A > epic::CovFold<2, false, false>::MAXA;
+  const bool many = A > epic::CovFold<2, false, epic::kCovPlain>::MAXA;
+  x->cov_kind = many ? epic::kCovMany : epic::kCovPlain;
   if (x->wide) {
-    if (!build_cov_programs<epic::CovFold<2, true, false>>(g, heads, prog)) return;
-  } else if (x->cov_dense || !build_cov_programs<epic::CovFold<2, false, false>>(g, heads, prog)) {
-    x->cov_dense = true;
-    if (!build_cov_programs<epic::CovFold<2, false, true>>(g, heads, prog)) return;
+    if (many ? !build_cov_programs<epic::CovFold<2, true, epic::kCovMany>>(g, heads, prog)
+             : !build_cov_programs<epic::CovFold<2, true, epic::kCovPlain>>(g, heads, prog))
+      return;
+  } else if (many ? !build_cov_programs<epic::CovFold<2, false, epic::kCovMany>>(g, heads, prog)
+                  : !build_cov_programs<epic::CovFold<2, false, epic::kCovPlain>>(g, heads, prog)) {
+    x->cov_kind = epic::kCovCrowded;
+    if (!build_cov_programs<epic::CovFold<2, false, epic::kCovCrowded>>(g, heads, prog)) return;
   }
-  x->cov_ap = (A + epic::kCovTile - 1) / epic::kCovTile * epic::kCovTile;
-  // shares per channel: whole rounds of resident workgroups, a share costing
-  // its antennas and about 6 more (program, first stage, output)
-  const int64_t slots = (int64_t)epic::covar::fold_blocks_per_cu(cov_shape(x)) * x->n_cu;
+  x->cov_fold_w = epic::covar::fold_blocks_per_cu(cov_shape(x)) * x->n_cu;
+  // the gradient's shares per channel: whole rounds of resident workgroups, a
+  // share costing its pairs and about four more steps (the table of H)
+  const int atiles = (A + 63) / 64;
   double best = 0;
-  for (int n = 1; n <= 32 && n * 4 <= std::max(A, 4); ++n) {
-    const double t = (double)(((int64_t)C * n + slots - 1) / slots) * ((A + n - 1) / n + 6);
-    if (n == 1 || t < best) {
-      best = t;
-      x->cov_chunks = n;
-    }
-  }
-  // the gradient's shares likewise; a share costs its pairs and about four
-  // more steps (the table of H)
-  const int P = x->cfg.n_pol, atiles = (A + 63) / 64;
   x->cov_ggroups = 8 / atiles;
   for (int n = 1; n <= 16; ++n) {
     const double t = (double)(((int64_t)C * P * n + 2 * x->n_cu - 1) / (2 * x->n_cu)) *
@@ -1649,13 +1705,13 @@ void build_cov(epic_ctx* x, const Geometry& g) {
       x->cov_gchunks = n;
     }
   }
-  const size_t vb = cov_v_bytes(x), rb = cov_r_bytes(x);
+  const size_t vb = cov_v_bytes(x);
   // the gradient's four planes (XX, YY, XY and YX) of every channel
   const size_t want = (P == 2 ? vb / 3 * 4 : vb) * C * (size_t)(C < 64 ? kCovMaxParts : 1);
   const size_t have = std::max(vb / 3 * 4, std::min(want, kCovWorkspace));
   x->cov_chan = (int)std::min<size_t>(C, have / vb);
   (void)hipGetLastError();
-  if (!x->cov_v.alloc(have) || !x->cov_r.alloc(rb * x->cov_chan) ||
+  if (!x->cov_v.alloc(have) || !x->cov_r.alloc(cov_r_bytes(x, x->cov_chan)) ||
       !x->cov_hat.alloc((size_t)x->cov_chan * P * N * N * sizeof(float4)) ||
       !x->cov_gpart.alloc((size_t)x->cov_chan * P * x->cov_gchunks * x->cov_ggroups * x->PA * sizeof(double2)) ||
       !x->cov_ants.alloc(ants.size() * sizeof(epic::CovAnt)) ||
@@ -1726,7 +1782,7 @@ bool use_cov(const epic_ctx* x, const uint8_t* efield, int64_t n_time) {
   const double C = x->cfg.n_chan, A = x->cfg.n_ant, ct = C * (double)n_time;
   const double direct = two ? 26.0 + ct * (wide ? 8.2e-3 + 1.15e-5 * A : 7.4e-3 + 0.84e-5 * A) + 2.4e-3 * std::min(ct, 4096.0)
                             : 18.7 + ct * ((wide ? 5.0e-3 : 4.2e-3) + 0.64e-5 * A) + 1.8e-3 * std::min(ct, 4096.0);
-  const double per_ant = two ? (x->cov_dense ? 6.0e-3 : 3.1e-3) + (wide ? (x->cov_dense ? 1.1e-3 : 2.4e-3) : 0.0)
+  const double per_ant = two ? (x->cov_kind != epic::kCovPlain ? 6.0e-3 : 3.1e-3) + (wide ? (x->cov_kind != epic::kCovPlain ? 1.1e-3 : 2.4e-3) : 0.0)
                              : (wide ? 1.6e-3 : 1.0e-3);
   const double cov = (two ? 39.0 + 0.10 * A : 29.0 + 0.12 * A) + C * (0.155 + per_ant * A) + cov_corr_us(x, efield, n_time);
   return cov < kCovMargin * direct;
@@ -1804,13 +1860,13 @@ epic_status run_cov(epic_ctx* x, const uint8_t* efield, int64_t n_time, const fl
     fa.head = x->cov_head.as<epic::CovProgHead>();
     fa.prog = x->cov_prog.p;
     fa.ants = x->cov_ants.as<epic::CovAnt>();
-    fa.r = x->cov_r.as<float2>();
+    fa.r = x->cov_r.as<double2>();
     fa.n_ant = A;
     fa.ap = x->cov_ap;
     fa.c0 = c0;
     fa.n_split = ns;
-    fa.n_chunk = x->cov_chunks;
-    fa.total = nc * x->cov_chunks;
+    fa.W = cov_fold_wgs(x, nc);
+    fa.units = (int64_t)nc * cov_groups(x) * A;
     epic::covar::launch_fold(fa, cov_shape(x), x->stream);
     epic::CovImageArgs ia;
     ia.r = fa.r;
@@ -1823,7 +1879,9 @@ epic_status run_cov(epic_ctx* x, const uint8_t* efield, int64_t n_time, const fl
     ia.autos = x->autos ? 1 : 0;
     ia.image = reinterpret_cast<double2*>(image);
     ia.c0 = c0;
-    ia.n_chunk = x->cov_chunks;
+    ia.W = fa.W;
+    ia.units = fa.units;
+    ia.wide = x->wide ? 1 : 0;
     ia.reset = reset ? 1 : 0;
     ia.transposed = x->transposed ? 1 : 0;
     epic::covar::launch_image(ia, P, nc, x->stream);
