@@ -51,13 +51,14 @@ int fold_blocks_per_cu(const Shape& s) {
   return std::max(1, nb);
 }
 
-void launch_corr(const CovCorrArgs& a, int n_pol, bool vec, hipStream_t stream) {
+void launch_corr(const CovCorrArgs& a, int n_pol, hipStream_t stream) {
+  const bool whole = a.n_ant % 4 == 0;
   auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3((unsigned)a.total), dim3(256), 0, stream, a); };
   if (n_pol == 2) {
-    if (vec) go(cov_corr_kernel<2, true>);
+    if (whole) go(cov_corr_kernel<2, true>);
     else go(cov_corr_kernel<2, false>);
   } else {
-    if (vec) go(cov_corr_kernel<1, true>);
+    if (whole) go(cov_corr_kernel<1, true>);
     else go(cov_corr_kernel<1, false>);
   }
 }

@@ -73,7 +73,9 @@ __host__ __device__ __forceinline__ int cov_tiles(int nb, int P) {
 // 1.1 POP/s of 8 operations per pair and sample; 8.9 vector instructions per
 // matrix one, of which about 4 are free, so the two take turns (matrix pipes 25 %,
 // vector ALU 31 % busy).
-template <int P, bool VEC>
+// Four antennas' samples are one load at any address (the hardware loads an
+// unaligned word); WHOLE: A % 4 = 0, no group of four reaches past its row.
+template <int P, bool WHOLE>
 __global__ __launch_bounds__(256, 2) void cov_corr_kernel(CovCorrArgs a) {
   __shared__ __align__(16) uint8_t lds[2][2 * kCovTile * kCovPitch];
   const int logical = wg_range_index(blockIdx.x, a.total, 1);
@@ -117,9 +119,12 @@ __global__ __launch_bounds__(256, 2) void cov_corr_kernel(CovCorrArgs a) {
   const int uwave = __builtin_amdgcn_readfirstlane(wave);
   const int n_row = (int)(t_end - t_begin);
   const uint8_t* src = a.efield + t_begin * tstride + (int64_t)(a.c0 + cl) * P * a.n_ant;
-  const uint32_t loff = ant < a.n_ant ? (uint32_t)(pol * a.n_ant + ant) : 0u;
   const int nvalid = a.n_ant - ant;    // antennas of the four that exist
   const uint32_t lmask = nvalid >= 4 ? ~0u : nvalid <= 0 ? 0u : (1u << (8 * nvalid)) - 1u;
+  // the row's last group reads its last four bytes and shifts them down
+  const int first = nvalid <= 0 ? 0 : WHOLE || nvalid >= 4 || a.n_ant < 4 ? ant : a.n_ant - 4;
+  const uint32_t loff = (uint32_t)(pol * a.n_ant + first);
+  const int lshift = nvalid > 0 ? 8 * (ant - first) : 0;
   const int n_stage = (int)((t_end - t_begin + kCovStage - 1) / kCovStage);
   auto load = [&](int k, uint32_t (&raw)[16]) {
     if (k >= n_stage) k = n_stage - 1;
@@ -128,12 +133,12 @@ __global__ __launch_bounds__(256, 2) void cov_corr_kernel(CovCorrArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const uint8_t* row = src + (k * kCovStage + 16 * uwave + (i < last ? i : last)) * tstride;
-      if (VEC) {
-        raw[i] = *reinterpret_cast<const uint32_t*>(row + loff);
-      } else {
+      if (WHOLE || a.n_ant >= 4) {
+        __builtin_memcpy(&raw[i], row + loff, 4);
+      } else {                         // one to three antennas
         raw[i] = 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 3; ++q)
           if (q < nvalid) raw[i] |= (uint32_t)row[loff + q] << (8 * q);
       }
     }
@@ -157,7 +162,7 @@ __global__ __launch_bounds__(256, 2) void cov_corr_kernel(CovCorrArgs a) {
       for (int s = 0; s < 4; ++s) {
         uint32_t in[4], tr[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) in[i] = raw[4 * s + i] & (4 * s + i < rows ? lmask : 0u);
+        for (int i = 0; i < 4; ++i) in[i] = (WHOLE ? raw[4 * s + i] : raw[4 * s + i] >> lshift) & (4 * s + i < rows ? lmask : 0u);
         transpose4(in, tr);
 #pragma unroll
         for (int q = 0; q < 4; ++q) u[q][s] = tr[q];
@@ -400,7 +405,7 @@ __device__ __forceinline__ void cov_fold_body(const CovFoldArgs& a, double2* con
       reinterpret_cast<const CovProgLane<S::STEPS, S::SLOTS>*>(a.prog)[(int64_t)(c * S::NW + wave) * 64 + lane];
   // E' offsets unpacked (opaque: else they are unpacked at every step), where
   // there are registers for it
-  constexpr bool UNPACK = KIND == kCovPlain;
+  constexpr bool UNPACK = KIND == kCovPlain || (WIDE && KIND == kCovMany);
   uint32_t eoff[UNPACK ? S::STEPS : 1];
   if constexpr (UNPACK) {
 #pragma unroll

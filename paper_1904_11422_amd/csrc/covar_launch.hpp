@@ -14,7 +14,7 @@ struct Shape {
 };
 
 int fold_blocks_per_cu(const Shape& s);
-void launch_corr(const CovCorrArgs& a, int n_pol, bool vec, hipStream_t stream);
+void launch_corr(const CovCorrArgs& a, int n_pol, hipStream_t stream);
 void launch_sum(const CovSumArgs& a, hipStream_t stream);
 void launch_fold(const CovFoldArgs& a, const Shape& s, hipStream_t stream);
 void launch_image(const CovImageArgs& a, int n_pol, int n_chan, hipStream_t stream);

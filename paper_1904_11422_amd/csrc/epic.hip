@@ -1753,53 +1753,77 @@ int cov_splits(const epic_ctx* x, int64_t n_time) {
   return best_n;
 }
 
-// Whether a call takes the covariance form: where its time is estimated below
-// three quarters of the direct form's.  Both are fitted (least squares of the
-// relative error, microseconds) to 6950 calls drawn over 1 and 2 polarisations,
-// 8 - 400 antennas, 1 - 132 channels, 64 - 1250 samples, N/2 and wide blocks,
-// timed both ways; the margin covers the fits' spread (10 % - 90 %: 0.85 - 1.14):
-// 0.2 % of the calls ended up slower than the direct form by over 3 %, against
-// 4 % with a margin of one tenth.  The direct kernels cost every sample of every
-// channel its transforms; the covariance form costs every channel its
-// antennas, almost whatever T is, over a longer chain of launches, and more
-// where the samples cannot be read four at a time (A % 4).  E.g. 256 dual-pol
-// antennas, T = 1000: 1166 against 314 at 132 channels, 173 / 84 at 16, 66 / 80
-// at 4; T = 64: 122 / 244 at 132.
-bool cov_vec(const epic_ctx* x, const uint8_t* efield) {
-  return x->cfg.n_ant % 4 == 0 && (reinterpret_cast<uintptr_t>(efield) & 3) == 0;
-}
-constexpr double kCovMargin = 0.75;
-double cov_corr_us(const epic_ctx* x, const uint8_t* efield, int64_t n_time) {
-  const double per_tile = (double)x->cfg.n_chan * n_time * epic::cov_tiles(x->cov_ap / epic::kCovTile, x->cfg.n_pol);
-  return cov_vec(x, efield) ? 4.5e-5 * per_tile : 4.2e-4 * per_tile + 0.03 * n_time;
-}
+// Whether a call takes the covariance form: where its estimated time is below
+// 0.96 of the direct form's less 12 us.  Both are fitted (non-negative least
+// squares of the relative error, microseconds) to 11604 calls drawn over 1 and 2
+// polarisations, 2 - 512 antennas, 1 - 132 channels, 64 - 131072 samples (a third
+// of them above 1250), N/2 and wide blocks, timed both ways; the margin covers the
+// fits' spread (10 % - 90 %: 0.9 - 1.1; launches count where the whole is short):
+// 0.1 % of the calls ended up slower than the direct form by over 3 %, the worst
+// by 14 %.  The direct kernels cost every sample of every channel its transforms;
+// the covariance form costs every channel its antennas and a pass of the samples,
+// over a longer chain of launches: the covariance kernel's rounds of stages (a few
+// channels fill few CUs, whatever T is) and the fold's antennas per workgroup.
+// E.g. 256 dual-pol antennas, T = 1000: 1200 against 387 at 132 channels, 66 / 113
+// at 4 (239 antennas); 94 antennas of one polarisation, one channel, T = 107322:
+// 538 / 840.
+// Neither estimate looks at the samples' address: the same call takes the same
+// form wherever its samples lie.
+bool cov_faster(double cov_us, double direct_us) { return cov_us < 0.96 * direct_us - 12.0; }
 bool cov_takes(const epic_ctx* x, int64_t n_time) {
   return x->cov && n_time >= 64 && n_time <= (int64_t)kCovMaxParts * epic::kCovMaxSplit;
 }
-bool use_cov(const epic_ctx* x, const uint8_t* efield, int64_t n_time) {
+// The covariance kernel's rounds of resident workgroups times stages each, and
+// the bytes (MB) of the splits that are added up.
+struct CovCorrCost {
+  double stages, mb;
+};
+CovCorrCost cov_corr_cost(const epic_ctx* x, int64_t n_time) {
+  const int64_t n = cov_splits(x, n_time), wgs = n * x->cfg.n_chan * epic::cov_tiles(x->cov_ap / epic::kCovTile, x->cfg.n_pol);
+  const int64_t stages = ((n_time + n - 1) / n + epic::kCovStage - 1) / epic::kCovStage;
+  return {(double)((wgs + 2 * x->n_cu - 1) / (2 * x->n_cu)) * (stages + 6),
+          n > 1 ? 1e-6 * n * x->cfg.n_chan * cov_v_bytes(x) : 0.0};
+}
+bool use_cov(const epic_ctx* x, int64_t n_time) {
   if (!cov_takes(x, n_time)) return false;
-  const bool two = x->cfg.n_pol == 2, wide = x->wide;
+  struct Fit {
+    double one, ct, cta, few;            // direct: per sample and channel, and antenna; the first 4096
+    double cone, ca, cc, step, stepa;    // covariance: per antenna, channel, antenna of a workgroup's range
+  };
+  static const Fit fits[2][2] = {{{18.3, 4.19e-3, 0.63e-5, 2.0e-3, 20.2, 0.096, 0.095, 0.31, 0.0},
+                                  {17.7, 4.75e-3, 0.70e-5, 2.2e-3, 17.6, 0.081, 0.101, 0.54, 0.4e-3}},
+                                 {{26.4, 7.47e-3, 0.83e-5, 2.3e-3, 31.1, 0.093, 0.268, 0.58, 3.0e-3},
+                                  {26.7, 8.27e-3, 1.22e-5, 2.4e-3, 23.3, 0.071, 0.316, 1.61, 5.4e-3}}};
+  const Fit& f = fits[x->cfg.n_pol - 1][x->wide];
   const double C = x->cfg.n_chan, A = x->cfg.n_ant, ct = C * (double)n_time;
-  const double direct = two ? 26.0 + ct * (wide ? 8.2e-3 + 1.15e-5 * A : 7.4e-3 + 0.84e-5 * A) + 2.4e-3 * std::min(ct, 4096.0)
-                            : 18.7 + ct * ((wide ? 5.0e-3 : 4.2e-3) + 0.64e-5 * A) + 1.8e-3 * std::min(ct, 4096.0);
-  const double per_ant = two ? (x->cov_kind != epic::kCovPlain ? 6.0e-3 : 3.1e-3) + (wide ? (x->cov_kind != epic::kCovPlain ? 1.1e-3 : 2.4e-3) : 0.0)
-                             : (wide ? 1.6e-3 : 1.0e-3);
-  const double cov = (two ? 39.0 + 0.10 * A : 29.0 + 0.12 * A) + C * (0.155 + per_ant * A) + cov_corr_us(x, efield, n_time);
-  return cov < kCovMargin * direct;
+  const double direct = f.one + ct * (f.ct + f.cta * A) + f.few * std::min(ct, 4096.0);
+  const CovCorrCost k = cov_corr_cost(x, n_time);
+  const double cov = f.cone + f.ca * A + f.cc * C +
+                     (f.step + f.stepa * A) * std::max(C * A / x->cov_fold_w, std::min(8.0, A)) +
+                     (A < 4 ? 5.0 : x->cfg.n_ant % 4 ? 1.98 : 1.32) * k.stages + 0.6 * k.mb;
+  return cov_faster(cov, direct);
 }
 
 // The same for the gradient, whose covariance form costs every channel its
 // pairs of antennas.  256 dual-pol antennas: 412 us direct, 83 here at 16
 // channels of 1250 samples, 304 / 150 at 64 of 200, 41 / 52 at 2 of 200.
-bool use_cov_backward(const epic_ctx* x, const uint8_t* efield, int64_t n_time) {
+bool use_cov_backward(const epic_ctx* x, int64_t n_time) {
   if (!cov_takes(x, n_time)) return false;
-  const bool two = x->cfg.n_pol == 2, wide = x->wide;
+  struct Fit {
+    double one, ct, cta, few;            // direct, as above
+    double cone, ca, cc, pairs;          // covariance: per antenna, channel, pair of a channel
+  };
+  static const Fit fits[2][2] = {{{14.7, 9.19e-3, 0.90e-5, 0.8e-3, 13.4, 0.033, 0.034, 0.94e-5},
+                                  {15.0, 10.19e-3, 1.09e-5, 0.7e-3, 12.4, 0.025, 0.037, 0.74e-5}},
+                                 {{15.5, 14.38e-3, 2.35e-5, 2.2e-3, 22.0, 0.012, 0.107, 2.43e-5},
+                                  {16.4, 15.82e-3, 3.82e-5, 2.4e-3, 21.3, 0.011, 0.105, 2.62e-5}}};
+  const Fit& f = fits[x->cfg.n_pol - 1][x->wide];
   const double C = x->cfg.n_chan, A = x->cfg.n_ant, ct = C * (double)n_time;
-  const double direct = two ? 15.8 + ct * (wide ? 17.0e-3 + 4.0e-5 * A : 15.1e-3 + 2.6e-5 * A)
-                            : 15.0 + ct * ((wide ? 11.2e-3 : 10.0e-3) + 1.2e-5 * A);
-  const double cov = (two ? 40.5 + 0.02 * A : 28.0 + 0.042 * A) + C * (0.093 + (two ? 2.3e-5 : 0.84e-5) * A * A) +
-                     cov_corr_us(x, efield, n_time);
-  return cov < kCovMargin * direct;
+  const double direct = f.one + ct * (f.ct + f.cta * A) + f.few * std::min(ct, 4096.0);
+  const CovCorrCost k = cov_corr_cost(x, n_time);
+  const double cov = f.cone + f.ca * A + C * (f.cc + f.pairs * A * A) +
+                     (A < 4 ? 4.5 : x->cfg.n_ant % 4 ? 1.95 : 1.45) * k.stages + 0.65 * k.mb;
+  return cov_faster(cov, direct);
 }
 
 // Time splits and channels per pass of a covariance call with n_prod planes.
@@ -1833,7 +1857,7 @@ epic::CovCorrArgs launch_cov_corr(epic_ctx* x, const CovPlan& p, const uint8_t* 
   a.n_split = p.splits;
   a.n_prod = n_prod;
   a.total = nc * p.splits * epic::cov_tiles(x->cov_ap / epic::kCovTile, P);
-  epic::covar::launch_corr(a, P, cov_vec(x, efield), x->stream);
+  epic::covar::launch_corr(a, P, x->stream);
   if (p.splits > 1) {
     epic::CovSumArgs sa;
     sa.v = a.v;
@@ -2527,7 +2551,7 @@ epic_status epic_image_accumulate(epic_ctx* x, const uint8_t* efield, int64_t n_
   (void)hipGetLastError();
   const epic_status s = x->cfg.precision != EPIC_FP32
                             ? run_split(x, efield, n_time, gains, image, reset)
-                        : use_cov(x, efield, n_time) ? run_cov(x, efield, n_time, gains, image, reset)
+                        : use_cov(x, n_time) ? run_cov(x, efield, n_time, gains, image, reset)
                             : run_fp32(x, efield, n_time, gains, image, reset, x->partial.as<double>());
   if (s != EPIC_OK) return s;
   return finish_accumulate(x, efield, n_time, gains, image);
@@ -2578,7 +2602,7 @@ epic_status epic_image_backward(epic_ctx* x, const uint8_t* efield, int64_t n_ti
   DeviceGuard guard(x->device);
   (void)hipGetLastError();               // an error of other code in this thread is not this call's
   if (!x->fused) return staged_backward(x, efield, n_time, gains, grad_image, grad_gains);
-  if (use_cov_backward(x, efield, n_time)) return cov_backward(x, efield, n_time, gains, grad_image, grad_gains);
+  if (use_cov_backward(x, n_time)) return cov_backward(x, efield, n_time, gains, grad_image, grad_gains);
   const int C = x->cfg.n_chan;
   // work units per channel: samples, or (parity, sample) pairs at N = 128
   const int64_t upc = x->cfg.grid_n == 128 ? 2 * n_time : n_time;

@@ -45,3 +45,55 @@ def test_gradient_ignores_an_older_error_of_the_thread(T):
     torch.cuda.synchronize()
     assert st == 0, message
     assert torch.equal(out, want)
+
+
+@pytest.mark.parametrize("seed,A,C,P,T", [(952, 256, 16, 2, 1250), (955, 64, 24, 1, 700), (956, 90, 20, 2, 500)])
+def test_samples_give_the_same_bits_at_any_address(seed, A, C, P, T):
+    """The same samples one byte further on: the same form, the same bits."""
+    import torch
+    inp = synth.random_problem(seed, 64, A, C, P, T, fill=0.45)
+    im = _imager(inp)
+    ef, g = _dev(inp)
+    rng = np.random.default_rng(seed)
+    gam = torch.from_numpy(rng.normal(size=im.image_shape()) + 0j).cuda()
+    want = im.accumulate(ef, g)
+    assert im.last_kernel_name() == "cov_fold_kernel"
+    grad = im.backward(ef, g, gam)
+    buf = torch.empty(ef.numel() + 4, dtype=torch.uint8, device="cuda")
+    for shift in (1, 2, 3):
+        odd = buf[shift:shift + ef.numel()].view(ef.shape)
+        odd.copy_(ef)
+        assert torch.equal(im.accumulate(odd, g), want)
+        assert im.last_kernel_name() == "cov_fold_kernel"
+        assert torch.equal(im.backward(odd, g, gam), grad)
+
+
+@pytest.mark.parametrize("A", [1, 2, 3, 5, 129])
+def test_last_samples_of_a_buffer(A):
+    """Rows of antennas that are no multiple of four, the last one at the very
+    end of its buffer: the tail is read within its row."""
+    import torch
+    import oracle
+    inp = synth.random_problem(957 + A, 64, A, 20, 1, 900, fill=0.45)
+    im = _imager(inp)
+    ef, g = _dev(inp)
+    got = im.accumulate(ef, g).cpu().numpy()
+    sub = synth.Inputs(64, 1, 1, A, 3, 0.5, 0.5, inp.xy_m, inp.freq_hz[19:], inp.gains[19:],
+                       np.ascontiguousarray(inp.efield[:, 19:]))
+    err = oracle.rel_errors(got[19:], oracle.image_from(sub)).max()
+    print(f"  A={A}: {im.last_kernel_name()} {err:.2e}", flush=True)
+    assert err <= 1e-5
+
+
+def test_long_integration_of_one_channel_stays_direct():
+    """One channel's covariances fill four workgroups however long it is: 94
+    antennas at T = 107322 take 538 us directly and 840 by them; six channels of
+    them gain."""
+    import torch
+    for C, route in ((1, "fused_image_kernel"), (6, "cov_fold_kernel")):
+        inp = synth.random_problem(963, 64, 96, C, 1, 4, fill=0.45)
+        im = _imager(inp)
+        T = 100_000 // (1 if C == 1 else 4)
+        ef = torch.zeros((T, C, 1, 96), dtype=torch.uint8, device="cuda")
+        im.accumulate(ef, torch.from_numpy(inp.gains).cuda())
+        assert im.last_kernel_name() == route
