@@ -198,7 +198,7 @@ epic_status enqueue_group(epic_batch* b, const BatchLaunch& L, hipStream_t s, co
   a.kblock = L.kblock;
   a.xcd = L.xcd;
   if (!launch_multi(L, dim3(a.W), s, a)) return b->fail(EPIC_E_UNSUPPORTED, "no multi-block kernel");
-  const int sub = fused_reduce_sub(L.N, n_time, a.total, a.W, a.team);
+  const int sub = fused_reduce_sub(L.N, L.P, L.C, n_time, a.total, a.W, a.team);
   const int64_t n = (int64_t)L.C * L.N * L.N, ppb = 256 / sub;
   const dim3 rgrid((unsigned)((n + ppb - 1) / ppb)), rblock(256);
   if (L.N == 128) {

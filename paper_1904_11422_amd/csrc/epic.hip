@@ -933,16 +933,20 @@ int64_t max_slot_count(int64_t segs, int64_t w_cap) {
 // float64 values per slot: NACC N^2 (N <= 64) or NACC N^2 / 2 (one parity at N = 128).
 size_t fused_slot_values(int N, int nacc) { return (size_t)nacc * N * N / (N == 128 ? 2 : 1); }
 
-// Sub-lanes of the fused reductions: parts per segment are about m times the
-// teams covering it (one long channel: up to one part per workgroup).  More
-// sub-lanes shorten a thread's chain of parts but leave its block fewer pixels,
-// and a part's values are read in runs of that many floats: 16 channels of 125
-// samples (33 parts of 64 KB a channel) took 16.4 us with 16 sub-lanes (64-byte
-// runs) and 12.4 with 4.  At 128 x 128 the two differ by less than 1 %, 16 ahead.
-int fused_reduce_sub(int N, int64_t n_time, int64_t units, int W, int m) {
+// Sub-lanes of the fused reductions of C channels: parts per segment are about m
+// times the teams covering it (one long channel: up to one part per workgroup).
+// More sub-lanes shorten a thread's chain of parts but leave its block fewer
+// pixels, and a part's values are read in runs of that many floats.  For 33 to 64
+// parts 4 are better than 16 only where blocks of 64 pixels still fill the chip:
+// whole calls of 24 antennas, 4 against 16, at N = 64 and one polarisation 27.1 /
+// 29.7 us (16 channels, T = 125), 23.9 / 23.3 (8), 15.0 / 12.7 (4), at two 44.0 /
+// 44.0, 39.2 / 36.9, 27.8 / 26.2; at N = 32 always 16.  At N = 128 a thread has twice
+// the products: one polarisation 31.7 / 36.4 (4 channels), two 48.6 / 43.1.
+int fused_reduce_sub(int N, int P, int C, int64_t n_time, int64_t units, int W, int m) {
   const int64_t parts = slots_per_channel(n_time, units, W / m) * m;
-  if (N == 128) return parts > 256 ? 64 : reduce_sub(parts);
-  return parts > 256 ? 64 : parts > 64 ? 16 : parts > 4 ? 4 : 1;
+  const int64_t blocks = (int64_t)C * N * N / 64;
+  if (parts > 256) return 64;
+  return parts > 32 && parts <= 64 && blocks >= (N == 128 && P == 2 ? 2048 : 1024) ? 4 : reduce_sub(parts);
 }
 
 bool launch_reduce(epic_ctx* x, const epic::ReduceArgs& a, bool thread_major) {
@@ -1998,7 +2002,7 @@ epic_status run_fp32(epic_ctx* x, const uint8_t* efield, int64_t n_time, const f
     r.team = a.team;
     r.kblock = a.kblock;
     r.reset = reset ? 1 : 0;
-    r.sub = fused_reduce_sub(N, n_time, a.total, a.W, a.team);
+    r.sub = fused_reduce_sub(N, P, C, n_time, a.total, a.W, a.team);
     const int64_t n = (int64_t)C * N * N, ppb = 256 / r.sub;
     if (P == 2)
       hipLaunchKernelGGL(epic::reduce_image128_kernel<2>, dim3((unsigned)((n + ppb - 1) / ppb)), dim3(256), 0,
@@ -2027,7 +2031,7 @@ epic_status run_fp32(epic_ctx* x, const uint8_t* efield, int64_t n_time, const f
     r.kblock = a.kblock;
     r.f32 = 1;
     r.reset = reset ? 1 : 0;
-    r.sub = fused_reduce_sub(N, n_time, total, a.W, a.team);
+    r.sub = fused_reduce_sub(N, P, C, n_time, total, a.W, a.team);
     r.autos = nullptr;
     r.K = x->cfg.kernel_support;
     r.autos_cpx = x->cpx ? 1 : 0;
