@@ -1462,12 +1462,13 @@ int cov_fold_wgs(const epic_ctx* x, int nc) {
 }
 
 constexpr size_t kCovWorkspace = (size_t)384 << 20;   // bytes of covariances at most
+constexpr size_t kCovSplitSpace = (size_t)128 << 20;  // ... of more than one split of every channel
 
 size_t cov_v_bytes(const epic_ctx* x) {               // one channel, one split
   return (size_t)(x->cfg.n_pol == 2 ? 3 : 1) * x->cov_ap * x->cov_ap * sizeof(int2);
 }
 size_t cov_r_bytes(const epic_ctx* x, int nc) {       // of a pass
-  return ((size_t)x->cov_fold_w + (size_t)nc * cov_groups(x)) * cov_slot_rows(x) * 64 * sizeof(double2);
+  return ((size_t)cov_fold_wgs(x, nc) + (size_t)nc * cov_groups(x)) * cov_slot_rows(x) * 64 * sizeof(double2);
 }
 
 // The fold's gridding program of one channel (CovProgHead).  The aperture's rows
@@ -1652,11 +1653,38 @@ bool build_cov_programs(const Geometry& g, std::vector<epic::CovProgHead>& heads
   return true;
 }
 
+// Time splits of the covariance kernel: its rounds of resident workgroups (0.9 us
+// per stage of 64 samples, 6 stages' worth of start and output) against the
+// planes written, read, added and read again at about 4 TB/s and one more launch.
+int cov_splits(const epic_ctx* x, int64_t n_time) {
+  const int64_t tiles = epic::cov_tiles(x->cov_ap / epic::kCovTile, x->cfg.n_pol);
+  const int64_t slots = 2 * (int64_t)x->n_cu;
+  const int64_t need = (n_time + epic::kCovMaxSplit - 1) / epic::kCovMaxSplit;
+  int best_n = (int)need;
+  double best = 0;
+  for (int64_t n = need; n <= kCovMaxParts; ++n) {
+    if (n > need && n * x->cfg.n_chan * cov_v_bytes(x) > x->cov_v.bytes) break;   // no room for all channels' splits
+    const int64_t stages = ((n_time + n - 1) / n + epic::kCovStage - 1) / epic::kCovStage;
+    const double t = (double)((x->cfg.n_chan * tiles * n + slots - 1) / slots) * (stages + 6) * 0.9 +
+                     (n == 1 ? 2.0 : 2.0 * n + 2.0) * x->cfg.n_chan * cov_v_bytes(x) / 4.0e6 + (n == 1 ? 0.0 : 6.0);
+    if (n == need || t < best) {
+      best = t;
+      best_n = (int)n;
+    }
+  }
+  return best_n;
+}
+
 // Tables and workspace of the covariance form for the current geometry; the
 // context runs without it if they cannot be had.
+void release_cov(epic_ctx* x) {
+  x->cov = false;
+  for (DevMem* m : {&x->cov_ants, &x->cov_v, &x->cov_r, &x->cov_head, &x->cov_prog, &x->cov_hat, &x->cov_gpart}) m->reset();
+}
+
 void build_cov(epic_ctx* x, const Geometry& g) {
   const int C = x->cfg.n_chan, A = x->cfg.n_ant, N = x->cfg.grid_n, K = x->cfg.kernel_support, P = x->cfg.n_pol;
-  x->cov = false;
+  release_cov(x);                       // of the geometry before
   if (!x->cov_allowed || !x->fused || N != 64 || K != 3 || x->cpx || A > 512) return;
   x->cov_ap = (A + epic::kCovTile - 1) / epic::kCovTile * epic::kCovTile;
   std::vector<epic::CovAnt> ants((size_t)C * A + epic::kCovAntsPast, epic::CovAnt{});
@@ -1709,10 +1737,12 @@ void build_cov(epic_ctx* x, const Geometry& g) {
       x->cov_gchunks = n;
     }
   }
-  const size_t vb = cov_v_bytes(x);
-  // the gradient's four planes (XX, YY, XY and YX) of every channel
-  const size_t want = (P == 2 ? vb / 3 * 4 : vb) * C * (size_t)(C < 64 ? kCovMaxParts : 1);
-  const size_t have = std::max(vb / 3 * 4, std::min(want, kCovWorkspace));
+  // V: the gradient's four planes (XX, YY, XY and YX) of every channel, and of few
+  // channels their time splits (a long integration of more takes fewer channels at
+  // a time; the most splits of one channel always fit)
+  const size_t vb = cov_v_bytes(x), vg = P == 2 ? vb / 3 * 4 : vb;
+  const size_t have = std::max({vg * kCovMaxParts, std::min(vg * C, kCovWorkspace),
+                                std::min(vg * C * kCovMaxParts, kCovSplitSpace)});
   x->cov_chan = (int)std::min<size_t>(C, have / vb);
   (void)hipGetLastError();
   if (!x->cov_v.alloc(have) || !x->cov_r.alloc(cov_r_bytes(x, x->cov_chan)) ||
@@ -1724,37 +1754,10 @@ void build_cov(epic_ctx* x, const Geometry& g) {
       hipMemcpy(x->cov_prog.p, prog.data(), prog.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(x->cov_ants.p, ants.data(), ants.size() * sizeof(epic::CovAnt), hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipGetLastError();
-    x->cov_v.reset();
-    x->cov_r.reset();
-    x->cov_ants.reset();
-    x->cov_head.reset();
-    x->cov_prog.reset();
-    x->cov_hat.reset();
-    x->cov_gpart.reset();
+    release_cov(x);
     return;
   }
   x->cov = true;
-}
-
-// Time splits of the covariance kernel: its rounds of resident workgroups (0.9 us
-// per stage of 64 samples, 6 stages' worth of start and output) against the
-// planes written, read, added and read again at about 4 TB/s and one more launch.
-int cov_splits(const epic_ctx* x, int64_t n_time) {
-  const int64_t tiles = epic::cov_tiles(x->cov_ap / epic::kCovTile, x->cfg.n_pol);
-  const int64_t slots = 2 * (int64_t)x->n_cu;
-  const int64_t need = (n_time + epic::kCovMaxSplit - 1) / epic::kCovMaxSplit;
-  int best_n = (int)need;
-  double best = 0;
-  for (int64_t n = need; n <= kCovMaxParts; ++n) {
-    const int64_t stages = ((n_time + n - 1) / n + epic::kCovStage - 1) / epic::kCovStage;
-    const double t = (double)((x->cfg.n_chan * tiles * n + slots - 1) / slots) * (stages + 6) * 0.9 +
-                     (n == 1 ? 2.0 : 2.0 * n + 2.0) * x->cfg.n_chan * cov_v_bytes(x) / 4.0e6 + (n == 1 ? 0.0 : 6.0);
-    if (n == need || t < best) {
-      best = t;
-      best_n = (int)n;
-    }
-  }
-  return best_n;
 }
 
 // Whether a call takes the covariance form: where its estimated time is below
@@ -2495,7 +2498,7 @@ epic_status epic_set_antennas_kernels(epic_ctx* x, const double* xy_m, const dou
     x->L = L;
     build_cov(x, g);
   } else {
-    x->cov = false;
+    release_cov(x);
     if (!alloc_staged(x)) return x->fail(EPIC_E_NOMEM, "staged workspace allocation failed");
     // per-cell CSR over the whole grid, entries in (antenna, tap) order
     const int npix = N * N, nnz = A * g.KK;
@@ -2774,8 +2777,7 @@ void epic_destroy(epic_ctx* x) {
     x->sp_partial.reset();
     x->au_part.reset(); x->au_tab.reset(); x->au_sums.reset(); x->au_wi.reset(); x->au_w.reset(); x->au_hat.reset();
     x->au_gauto.reset();
-    x->cov_ants.reset(); x->cov_v.reset(); x->cov_r.reset(); x->cov_head.reset(); x->cov_prog.reset();
-    x->cov_hat.reset(); x->cov_gpart.reset();
+    release_cov(x);
   }
   delete x;
 }

@@ -97,3 +97,24 @@ def test_long_integration_of_one_channel_stays_direct():
         ef = torch.zeros((T, C, 1, 96), dtype=torch.uint8, device="cuda")
         im.accumulate(ef, torch.from_numpy(inp.gains).cuda())
         assert im.last_kernel_name() == route
+
+
+def test_workspace_goes_with_a_geometry_that_cannot_use_it():
+    """The caller's own kernels, and apertures beyond the fused kernels' blocks,
+    never take the covariance form: what it held (its covariances alone are
+    over 200 MB at this shape) is free again, and comes back with the Gaussian."""
+    import torch
+    inp = synth.random_problem(954, 64, 256, 132, 2, 1, fill=0.45)
+    im = _imager(inp)
+    torch.cuda.synchronize()
+    held = torch.cuda.mem_get_info()[0]
+    im.set_antennas(inp.xy_m, inp.freq_hz, kernels=np.ones((132, 256, 3, 3), np.complex64))
+    assert torch.cuda.mem_get_info()[0] - held > 200 << 20
+    im.set_antennas(inp.xy_m, inp.freq_hz)
+    assert abs(torch.cuda.mem_get_info()[0] - held) < 64 << 20
+    few_inp = synth.random_problem(965, 64, 256, 60, 2, 1, fill=0.45)         # fewer channels hold less
+    few = _imager(few_inp)
+    without = torch.cuda.mem_get_info()[0]
+    few.set_antennas(few_inp.xy_m, few_inp.freq_hz, kernels=np.ones((60, 256, 3, 3), np.complex64))
+    assert torch.cuda.mem_get_info()[0] - without < 240 << 20
+    few.close()
