@@ -1833,7 +1833,9 @@ bool use_cov_backward(const epic_ctx* x, int64_t n_time) {
   return cov_faster(cov, direct);
 }
 
-// Time splits and channels per pass of a covariance call with n_prod planes.
+// Time splits and channels per pass of a covariance call with n_prod planes; the
+// passes are equal (264 channels of 256 dual-pol antennas as 132 + 132, not 256
+// and 8 that pay the whole chain of latencies).
 struct CovPlan {
   int splits, chans;
   int64_t t_split;
@@ -1844,7 +1846,10 @@ CovPlan cov_plan(const epic_ctx* x, int64_t n_time, int n_prod) {
   p.t_split = ((n_time + p.splits - 1) / p.splits + epic::kCovStage - 1) / epic::kCovStage * epic::kCovStage;
   p.splits = (int)((n_time + p.t_split - 1) / p.t_split);
   const int64_t bytes = (int64_t)n_prod * x->cov_ap * x->cov_ap * sizeof(int2) * p.splits;
-  p.chans = (int)std::max<int64_t>(1, std::min<int64_t>(x->cov_chan, (int64_t)x->cov_v.bytes / bytes));
+  const int C = x->cfg.n_chan;
+  const int most = (int)std::max<int64_t>(1, std::min<int64_t>(x->cov_chan, (int64_t)x->cov_v.bytes / bytes));
+  const int passes = (C + most - 1) / most;
+  p.chans = (C + passes - 1) / passes;
   return p;
 }
 

@@ -75,28 +75,27 @@ def _imager(inp, **kw):
     return im
 
 
-def _check(inp, channels, image=True, gradient=True):
+def _check(inp, channels):
     import torch
     im = _imager(inp)
     ef = torch.from_numpy(np.ascontiguousarray(inp.efield)).cuda()
     g = torch.from_numpy(np.ascontiguousarray(inp.gains)).cuda()
     print(f"  A={inp.n_ant} C={inp.n_chan} P={inp.n_pol} T={inp.n_time}", flush=True)
-    if image:
-        got = im.accumulate(ef, g).cpu().numpy()
-        assert im.last_kernel_name() == "cov_fold_kernel"
-        for c in channels:
-            err = oracle.rel_errors(got[c:c + 1], _image(_channel(inp, c))).max()
-            assert err <= TOL_FP32, f"image, channel {c}: {err:.3e}"
-        im.accumulate(ef, g, image=(twice := torch.from_numpy(got).cuda()), reset=False)
-        assert np.array_equal(twice.cpu().numpy(), 2 * got)
-    if gradient:
-        rng = np.random.default_rng(inp.n_ant)
-        gam = rng.normal(size=im.image_shape()) + 1j * rng.normal(size=im.image_shape())
-        got = im.backward(ef, g, torch.from_numpy(gam).cuda()).cpu().numpy()
-        for c in channels:
-            want = _gradient(_channel(inp, c), gam[c])
-            err = np.linalg.norm(got[c:c + 1] - want) / np.linalg.norm(want)
-            assert err <= TOL_GRAD, f"gradient, channel {c}: {err:.3e}"
+    got = im.accumulate(ef, g).cpu().numpy()
+    assert im.last_kernel_name() == "cov_fold_kernel"
+    for c in channels:
+        err = oracle.rel_errors(got[c:c + 1], _image(_channel(inp, c))).max()
+        assert err <= TOL_FP32, f"image, channel {c}: {err:.3e}"
+    twice = torch.from_numpy(got).cuda()
+    im.accumulate(ef, g, image=twice, reset=False)
+    assert np.array_equal(twice.cpu().numpy(), 2 * got)
+    rng = np.random.default_rng(inp.n_ant)
+    gam = rng.normal(size=im.image_shape()) + 1j * rng.normal(size=im.image_shape())
+    got = im.backward(ef, g, torch.from_numpy(gam).cuda()).cpu().numpy()
+    for c in channels:
+        want = _gradient(_channel(inp, c), gam[c])
+        err = np.linalg.norm(got[c:c + 1] - want) / np.linalg.norm(want)
+        assert err <= TOL_GRAD, f"gradient, channel {c}: {err:.3e}"
 
 
 @pytest.mark.gpu
@@ -108,3 +107,37 @@ def _check(inp, channels, image=True, gradient=True):
 ])
 def test_time_splits(seed, A, C, P, T, fill):
     _check(synth.random_problem(seed, 64, A, C, P, T, fill=fill), [0, C - 1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("seed,A,C,P,T,fill", [
+    (965, 512, 67, 2, 800, 0.48),      # V of 61 channels fits (45 with the gradient's planes): two ragged passes
+    (966, 500, 50, 2, 1000, 0.70),     # wide block; the gradient in two passes
+])
+def test_passes_over_the_channels(seed, A, C, P, T, fill):
+    """More channels than the workspace holds: the passes reuse it, channels on
+    both sides of every seam."""
+    _check(synth.random_problem(seed, 64, A, C, P, T, fill=fill), [0, C // 2 - 1, C // 2, C // 2 + 1, C - 1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("seed,A,C,P,T,fill", [
+    (967, 512, 6, 1, 3000, 0.48),      # eight tiles of a, one share of b per workgroup
+    (968, 300, 20, 1, 900, 0.66),      # wide block, more than 256 antennas, one polarisation
+    (969, 4, 60, 2, 600, 0.66),        # ranges of a few antennas, several channels per workgroup
+    (970, 3, 200, 1, 500, 0.45),
+    (971, 101, 3, 2, 9000, 0.45),      # few channels: a channel's antennas over many workgroups
+    (972, 120, 30, 2, 700, 0.2),       # crowded cells: the fold's longest program
+])
+def test_edges_of_antennas_and_channels(seed, A, C, P, T, fill):
+    _check(synth.random_problem(seed, 64, A, C, P, T, fill=fill), [0, C // 2, C - 1])
+
+
+@pytest.mark.gpu
+def test_cells_of_more_antennas_than_a_program_holds_stay_direct():
+    import torch
+    inp = synth.random_problem(973, 64, 200, 30, 2, 600, fill=0.12, min_sep_cells=0.1)
+    im = _imager(inp)
+    got = im.accumulate(torch.from_numpy(inp.efield).cuda(), torch.from_numpy(inp.gains).cuda()).cpu().numpy()
+    assert im.last_kernel_name() == "fused_image_kernel"
+    assert oracle.rel_errors(got[:1], _image(_channel(inp, 0))).max() <= TOL_FP32
