@@ -280,8 +280,16 @@ epic_status epic_timing_history(epic_ctx *ctx, int32_t n, float *main_ms);
  * milliseconds.  Errors: EPIC_E_STATE (no such call yet). */
 epic_status epic_last_autos_timing(epic_ctx *ctx, float *sum_kernel_ms, float *removal_ms);
 
-/* Name of the main kernel the last imaging call launched (static string). */
+/* Name of the main kernel the last imaging or gradient call launched (static
+ * string).  Gradients report "adjoint_kernel" (64 x 64 and smaller) whatever
+ * their form, "adjoint_wide_kernel" and "adjoint128_kernel" for the direct
+ * form's other variants: epic_last_form tells the forms apart. */
 const char *epic_last_kernel_name(const epic_ctx *ctx);
+
+/* Form the last imaging or gradient call took (static string): "direct" (every
+ * sample transformed), "covariance" (the antennas' covariances, then the image or
+ * gradient once per channel), "staged", "split" or "none". */
+const char *epic_last_form(const epic_ctx *ctx);
 
 /* ------------------------------------------------------------------------
  * Front end and streaming ingest (Sec. 3.2 and Fig. 2: the channelised

@@ -228,6 +228,10 @@ class Imager:
     def last_kernel_name(self) -> str:
         return self.L.epic_last_kernel_name(self._ctx).decode()
 
+    def last_form(self) -> str:
+        """"direct", "covariance", "staged", "split" or "none": the form of the last call."""
+        return self.L.epic_last_form(self._ctx).decode()
+
     def close(self):
         if getattr(self, "_ctx", None):
             self.L.epic_destroy(self._ctx)

@@ -20,7 +20,7 @@ EXPORTS = ("epic_init", "epic_set_stream", "epic_set_antennas", "epic_set_antenn
            "epic_gridding_program",
            "epic_image_accumulate", "epic_image_accumulate_noalloc",
            "epic_image_backward", "epic_last_timing", "epic_timing_history", "epic_last_autos_timing",
-           "epic_last_kernel_name",
+           "epic_last_kernel_name", "epic_last_form",
            "epic_destroy", "epic_last_error",
            "epic_batch_create", "epic_batch_set_antennas", "epic_batch_accumulate",
            "epic_batch_capture", "epic_batch_replay", "epic_batch_tune", "epic_batch_plan",
@@ -91,6 +91,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     L.epic_last_autos_timing.restype = ctypes.c_int
     L.epic_last_kernel_name.argtypes = [vp]
     L.epic_last_kernel_name.restype = ctypes.c_char_p
+    L.epic_last_form.argtypes = [vp]
+    L.epic_last_form.restype = ctypes.c_char_p
     L.epic_destroy.argtypes = [vp]
     L.epic_destroy.restype = None
     L.epic_last_error.argtypes = [vp]

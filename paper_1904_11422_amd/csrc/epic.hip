@@ -157,6 +157,7 @@ struct epic_ctx {
   int tb_override = 0;                // tuned staged batch (0: tb)
   int adj_w = 0;
   const char* last_kernel = "none";
+  const char* last_form = "none";      // epic_last_form
 
   // tables
   bool have_geom = false;
@@ -1198,6 +1199,7 @@ epic_status run_split(epic_ctx* x, const uint8_t* efield, int64_t n_time, const 
   mark_main_begin(x);
   split_dispatch(P, bf, qb, SplitLaunch{x, &sa, grid, vec});
   x->last_kernel = "split_image_kernel";
+  x->last_form = "split";
   mark_main_end(x);
   epic::SplitReduceArgs ra;
   ra.partial = x->sp_partial.as<double>();
@@ -1812,23 +1814,25 @@ bool use_cov(const epic_ctx* x, int64_t n_time) {
 }
 
 // The same for the gradient, whose covariance form costs every channel its
-// pairs of antennas.  256 dual-pol antennas: 412 us direct, 83 here at 16
+// pairs of antennas, in tiles of 64 by what a workgroup's eight waves hold of them
+// (kept whole: five tiles leave three waves idle).  Fitted to 6397 calls, likewise:
+// 0.1 % slower by over 3 %, the worst by 11 %.  256 dual-pol antennas: 412 us direct, 83 here at 16
 // channels of 1250 samples, 304 / 150 at 64 of 200, 41 / 52 at 2 of 200.
 bool use_cov_backward(const epic_ctx* x, int64_t n_time) {
   if (!cov_takes(x, n_time)) return false;
   struct Fit {
     double one, ct, cta, few;            // direct, as above
-    double cone, ca, cc, pairs;          // covariance: per antenna, channel, pair of a channel
+    double cone, ca, cc, pairs;          // covariance: per antenna, channel, 512 lanes' pairs with one b
   };
-  static const Fit fits[2][2] = {{{14.7, 9.19e-3, 0.90e-5, 0.8e-3, 13.4, 0.033, 0.034, 0.94e-5},
-                                  {15.0, 10.19e-3, 1.09e-5, 0.7e-3, 12.4, 0.025, 0.037, 0.74e-5}},
-                                 {{15.5, 14.38e-3, 2.35e-5, 2.2e-3, 22.0, 0.012, 0.107, 2.43e-5},
-                                  {16.4, 15.82e-3, 3.82e-5, 2.4e-3, 21.3, 0.011, 0.105, 2.62e-5}}};
+  static const Fit fits[2][2] = {{{14.7, 9.19e-3, 0.90e-5, 0.8e-3, 13.4, 0.035, 0.031, 3.67e-3},
+                                  {15.0, 10.19e-3, 1.09e-5, 0.7e-3, 12.6, 0.025, 0.029, 2.92e-3}},
+                                 {{15.5, 14.38e-3, 2.35e-5, 2.2e-3, 21.7, 0.011, 0.109, 8.97e-3},
+                                  {16.4, 15.82e-3, 3.82e-5, 2.4e-3, 21.2, 0.013, 0.099, 9.15e-3}}};
   const Fit& f = fits[x->cfg.n_pol - 1][x->wide];
   const double C = x->cfg.n_chan, A = x->cfg.n_ant, ct = C * (double)n_time;
   const double direct = f.one + ct * (f.ct + f.cta * A) + f.few * std::min(ct, 4096.0);
   const CovCorrCost k = cov_corr_cost(x, n_time);
-  const double cov = f.cone + f.ca * A + C * (f.cc + f.pairs * A * A) +
+  const double cov = f.cone + f.ca * A + C * (f.cc + f.pairs * A / x->cov_ggroups) +
                      (A < 4 ? 4.5 : x->cfg.n_ant % 4 ? 1.95 : 1.45) * k.stages + 0.65 * k.mb;
   return cov_faster(cov, direct);
 }
@@ -1923,6 +1927,7 @@ epic_status run_cov(epic_ctx* x, const uint8_t* efield, int64_t n_time, const fl
     epic::covar::launch_image(ia, P, nc, x->stream);
   }
   x->last_kernel = "cov_fold_kernel";
+  x->last_form = "covariance";
   mark_main_end(x);
   if (x->autos && x->timing) {                       // no kernel of its own: the fold leaves the terms out
     (void)hipEventRecord(x->ev[3], x->stream);
@@ -1971,7 +1976,8 @@ epic_status cov_backward(epic_ctx* x, const uint8_t* efield, int64_t n_time, con
     sa.n = (int64_t)nc * x->PA;
     epic::covar::launch_grad_sum(sa, P, x->stream);
   }
-  x->last_kernel = "adjoint_kernel";
+  x->last_kernel = "adjoint_kernel";            // as gradients report (epic_last_form tells)
+  x->last_form = "covariance";
   mark_main_end(x);
   if (x->timing) {
     (void)hipEventRecord(x->ev[2], x->stream);
@@ -1997,6 +2003,7 @@ epic_status run_fp32(epic_ctx* x, const uint8_t* efield, int64_t n_time, const f
     a.team = fg.team;
     if (!launch_fused128(x, a)) return x->fail(EPIC_E_UNSUPPORTED, "no fused kernel for this shape");
     x->last_kernel = "fused_image128_kernel";
+    x->last_form = "direct";
     mark_main_end(x);
     epic::Reduce128Args r;
     r.partial = partial;
@@ -2025,6 +2032,7 @@ epic_status run_fp32(epic_ctx* x, const uint8_t* efield, int64_t n_time, const f
     a.team = fg.team;
     if (!launch_fused(x, a)) return x->fail(EPIC_E_UNSUPPORTED, "no fused kernel for this shape");
     x->last_kernel = x->wide ? "fused_wide_image_kernel" : "fused_image_kernel";
+    x->last_form = "direct";
     mark_main_end(x);
     epic::ReduceArgs r;
     r.partial = partial;
@@ -2095,6 +2103,7 @@ epic_status run_fp32(epic_ctx* x, const uint8_t* efield, int64_t n_time, const f
                            dim3(256), 0, x->stream, ac);
     }
     x->last_kernel = "staged_fft_kernel";
+    x->last_form = "staged";
     mark_main_end(x);
     epic::ReduceArgs r;
     r.partial = x->st_acc.as<double>();
@@ -2194,6 +2203,7 @@ epic_status staged_backward(epic_ctx* x, const uint8_t* efield, int64_t n_time, 
                        dim3(256), 0, x->stream, dg);
   }
   x->last_kernel = "staged_degrid_kernel";
+  x->last_form = "staged";
   mark_main_end(x);
   if (x->autos) launch_autos_grad(x, efield, n_time, gains, grad_image);
   // 2 dL/dg* (minus the autocorrelation term) from the single slot per channel
@@ -2656,6 +2666,7 @@ epic_status epic_image_backward(epic_ctx* x, const uint8_t* efield, int64_t n_ti
   a.W = (int)std::min<int64_t>(aw, total);
   if (!launch_adjoint(x, a)) return x->fail(EPIC_E_UNSUPPORTED, "no adjoint kernel for this shape");
   x->last_kernel = x->cfg.grid_n == 128 ? "adjoint128_kernel" : x->wide ? "adjoint_wide_kernel" : "adjoint_kernel";
+  x->last_form = "direct";
   mark_main_end(x);
   if (x->autos) launch_autos_grad(x, efield, n_time, gains, grad_image);
   epic::GradReduceArgs r;
@@ -2764,6 +2775,7 @@ epic_status epic_kernel_taper(epic_ctx* x, double* taper) {
 }
 
 const char* epic_last_kernel_name(const epic_ctx* x) { return x ? x->last_kernel : "none"; }
+const char* epic_last_form(const epic_ctx* x) { return x ? x->last_form : "none"; }
 
 void epic_destroy(epic_ctx* x) {
   if (!x) return;

@@ -92,6 +92,7 @@ def _check(inp, channels):
     rng = np.random.default_rng(inp.n_ant)
     gam = rng.normal(size=im.image_shape()) + 1j * rng.normal(size=im.image_shape())
     got = im.backward(ef, g, torch.from_numpy(gam).cuda()).cpu().numpy()
+    assert im.last_form() == "covariance"
     for c in channels:
         want = _gradient(_channel(inp, c), gam[c])
         err = np.linalg.norm(got[c:c + 1] - want) / np.linalg.norm(want)
