@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <array>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -13,6 +14,7 @@
 #include <mutex>
 #include <queue>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -45,6 +47,8 @@ struct DevMem {
     p = nullptr;
     bytes = 0;
   }
+  // at least n bytes: what is there if it is no more than twice that
+  bool reuse(size_t n) { return (p && bytes >= n && bytes <= 2 * n) || alloc(n); }
   bool alloc(size_t n) {
     reset();
     if (n == 0) n = 16;
@@ -62,7 +66,7 @@ struct Geometry {
   std::vector<int> tcell;             // [C][A][KK] the same taps translated to start at (0, 0)
   std::vector<float> w;               // [C][A][KK] (real parts for complex kernels)
   std::vector<float> wi;              // [C][A][KK] imaginary parts, empty for real kernels
-  std::vector<double> wj, wx;         // [C][A][K] the Gaussian's row and column factors (w = wj wx)
+  std::vector<double> off;            // [C][A][2] first tap's column and row, less the antenna's (Gaussian)
   bool fits_half = true;              // every channel's taps fit an N/2 x N/2 block
   bool fits_wide = true;              // ... a 3N/4 x 3N/4 block (the wide fused variant,
                                       // whose rows orient_wide then trims)
@@ -306,9 +310,7 @@ epic_status build_geometry(const epic_config& cfg, const double* xy, const doubl
     for (size_t o = 0; o < 2 * (size_t)C * A * K * K; ++o)
       if (!std::isfinite(kernels[o])) { m = "kernel value is not finite"; return EPIC_E_INVALID; }
   }
-  const int K1 = kernels ? 0 : K;
-  g.wj.assign((size_t)C * A * K1, 0.0);
-  g.wx.assign((size_t)C * A * K1, 0.0);
+  g.off.assign(kernels ? 0 : (size_t)C * A * 2, 0.0);
   g.fits_half = true;
   g.fits_wide = true;
   g.ext_j = g.ext_i = 0;
@@ -328,10 +330,9 @@ epic_status build_geometry(const epic_config& cfg, const double* xy, const doubl
         m = buf;
         return EPIC_E_OFFGRID;
       }
-      for (int d = 0; d < K1; ++d) {
-        const double di = i0 - h + d - X, dj = j0 - h + d - Y;
-        g.wj[((size_t)c * A + a) * K + d] = std::exp(-dj * dj * inv2s2);
-        g.wx[((size_t)c * A + a) * K + d] = std::exp(-di * di * inv2s2);
+      if (!kernels) {
+        g.off[2 * ((size_t)c * A + a)] = i0 - h - X;
+        g.off[2 * ((size_t)c * A + a) + 1] = j0 - h - Y;
       }
       int k = 0;
       for (int dj = -h; dj <= h; ++dj)
@@ -359,6 +360,33 @@ epic_status build_geometry(const epic_config& cfg, const double* xy, const doubl
       g.tcell[o] = (g.cell[o] / N - jmin) * N + (g.cell[o] % N - imin);
   }
   return EPIC_OK;
+}
+
+// f(state, i) for i < n on several threads, each with a state of its own; false
+// if some f returned false or threw (no exception leaves a thread or this call).
+template <typename State, typename F> bool parallel_for(int n, State&& state, F&& f) {
+  std::atomic<int> next{0};
+  std::atomic<bool> ok{true};
+  auto work = [&] {
+    try {
+      auto own = state();
+      for (int i; ok && (i = next++) < n;)
+        if (!f(own, i)) ok = false;
+    } catch (...) {
+      ok = false;
+    }
+  };
+  // a channel's programs take 60 to 500 us, a thread about 20 to start
+  const int most = std::min<int>(16, (int)std::thread::hardware_concurrency());
+  std::vector<std::thread> threads;
+  try {
+    threads.reserve(std::max(0, most - 1));
+    for (int t = 1; t < std::min(most, n / 2); ++t) threads.emplace_back(work);
+  } catch (...) {                      // fewer threads then
+  }
+  work();
+  for (std::thread& t : threads) t.join();
+  return ok;
 }
 
 // Gridding programs of the fused kernels, per channel: a header row with the
@@ -451,8 +479,8 @@ void build_programs(const Geometry& g, int P, int gpt, std::vector<uint32_t>& ou
   std::vector<std::vector<float>> wims(cpx ? (size_t)C * NT : 0);
   std::vector<int32_t> header((size_t)C * NT, -1), header2((size_t)C * NT, -1);
   std::vector<int> wave_steps((size_t)C * NWAVE, 0);
-  L = 1;
-  for (int c = 0; c < C; ++c) {
+  std::atomic<int> longest{1};
+  auto channel = [&](int c) {
     std::vector<Run> cells(HR * HC);
     for (int j = 0; j < HR; ++j)
       for (int i = 0; i < HC; ++i) cells[j * HC + i].cell = SH::phys_row(j) * RS + i;
@@ -513,11 +541,7 @@ void build_programs(const Geometry& g, int P, int gpt, std::vector<uint32_t>& ou
                 bs = sl;
                 break;
               }
-          if (bw < 0) {                                // not reached: the classes fill every slot
-            out.clear();
-            L = 0;
-            return;
-          }
+          if (bw < 0) return false;                    // not reached: the classes fill every slot
           row_of[bw][bs] = j;
           wave_load[bw] += row_load[j];
         }
@@ -601,7 +625,8 @@ void build_programs(const Geometry& g, int P, int gpt, std::vector<uint32_t>& ou
           load[64 * w + l] = spat_ld[w][l];
         }
     const int Lc = std::max(1, *std::max_element(load.begin(), load.end()));
-    L = std::max(L, Lc);
+    for (int seen = longest; seen < Lc && !longest.compare_exchange_weak(seen, Lc);) {
+    }
     // each wave stops after its own longest lane (the later steps of its
     // lanes are padding), rounded like L to whole chunks past the fixed forms
     for (int w = 0; w < NWAVE; ++w) {
@@ -717,7 +742,14 @@ void build_programs(const Geometry& g, int P, int gpt, std::vector<uint32_t>& ou
         }
       }
     }
+    return true;
+  };
+  if (!parallel_for(C, [] { return 0; }, [&](int, int c) { return channel(c); })) {
+    out.clear();
+    L = 0;
+    return;
   }
+  L = longest;
   if (L > epic::kMaxFixedSteps) L = (L + epic::kStepChunk - 1) / epic::kStepChunk * epic::kStepChunk;
   out.assign((size_t)C * (L + 1) * NT * 2, 0u);
   if (cpx) out_im->assign((size_t)C * (L + 1) * NT, 0.f);
@@ -1520,13 +1552,14 @@ template <typename S> struct CovProgramBuilder {
     return slots;
   }
 
-  bool channel(int c, epic::CovProgHead* heads, Lane* lanes) {
+  // wj, wx: the channel's row and column factors of the kernels [A][K]
+  bool channel(int c, const double* wj, const double* wx, epic::CovProgHead* heads, Lane* lanes) {
     for (auto& v : cells) v.clear();
     for (int a = 0; a < g.A; ++a)
       for (int k = 0; k < g.KK; ++k) {
-        const size_t o = ((size_t)c * g.A + a) * g.KK + k, f = ((size_t)c * g.A + a) * K;
+        const size_t o = ((size_t)c * g.A + a) * g.KK + k, f = (size_t)a * K;
         cells[(size_t)(g.tcell[o] / N) * cols + g.tcell[o] % N].push_back(
-            {epic::cov_slot(a), g.wj[f + k / K] * g.wx[f + k % K]});
+            {epic::cov_slot(a), wj[f + k / K] * wx[f + k % K]});
       }
     count[0].fill(0);
     for (int j = 0; j < rows; ++j) {
@@ -1639,20 +1672,65 @@ template <typename S> struct CovProgramBuilder {
   }
 };
 
+// The antennas' table and the programs of every channel.
 template <typename S>
-bool build_cov_programs(const Geometry& g, std::vector<epic::CovProgHead>& heads, std::vector<uint32_t>& words) {
+bool build_cov_tables(const Geometry& g, int ap, double sigma, std::vector<epic::CovAnt>& ants,
+                      std::vector<epic::CovProgHead>& heads, std::vector<uint32_t>& words) {
   using Builder = CovProgramBuilder<S>;
   using Lane = typename Builder::Lane;
+  constexpr int K = Builder::K;
+  const int A = g.A, N = 64;
+  ants.assign((size_t)g.C * A + epic::kCovAntsPast, epic::CovAnt{});
   heads.assign((size_t)g.C * S::NW, epic::CovProgHead{});
   Lane idle{};                                         // steps past a wave's last read a zero slot
   for (uint32_t& e : idle.e) e = 0x10001u * (uint32_t)(Builder::kZero * sizeof(double2));
-  std::vector<Lane> prog((size_t)g.C * S::NW * 64, idle);
-  Builder b(g);
-  for (int c = 0; c < g.C; ++c)
-    if (!b.channel(c, &heads[(size_t)c * S::NW], &prog[(size_t)c * S::NW * 64])) return false;
-  words.resize(prog.size() * sizeof(Lane) / 4);
-  std::memcpy(words.data(), prog.data(), words.size() * 4);
-  return true;
+  static_assert(sizeof(Lane) % 4 == 0, "uploaded as words");
+  const size_t lane_words = sizeof(Lane) / 4, chan_words = (size_t)S::NW * 64 * lane_words;
+  words.resize(g.C * chan_words);
+  struct Own {
+    Builder b;
+    std::vector<Lane> lanes;
+    std::vector<double> wj, wx;
+    std::vector<int> order;
+  };
+  auto state = [&] {
+    return Own{Builder(g), std::vector<Lane>((size_t)S::NW * 64), std::vector<double>((size_t)A * K),
+               std::vector<double>((size_t)A * K), std::vector<int>(A)};
+  };
+  const double inv2s2 = 1.0 / (2.0 * sigma * sigma);
+  return parallel_for(g.C, state, [&](Own& own, int c) {
+    for (int a = 0; a < A; ++a)
+      for (int d = 0; d < K; ++d) {
+        const double* o = &g.off[2 * ((size_t)c * A + a)];
+        own.wx[(size_t)a * K + d] = std::exp(-(o[0] + d) * (o[0] + d) * inv2s2);
+        own.wj[(size_t)a * K + d] = std::exp(-(o[1] + d) * (o[1] + d) * inv2s2);
+      }
+    // the programs' aperture may be transposed: rows of taps are its columns then
+    if (g.transposed) own.wj.swap(own.wx);
+    const int* cell = &g.tcell[(size_t)c * A * g.KK];
+    for (int a = 0; a < A; ++a) own.order[a] = a;
+    std::stable_sort(own.order.begin(), own.order.end(),
+                     [&](int p, int q) { return cell[(size_t)p * g.KK] % N < cell[(size_t)q * g.KK] % N; });
+    for (int i = 0; i < A; ++i) {
+      epic::CovAnt& t = ants[(size_t)c * A + i];
+      const int a = own.order[i];
+      t.ant = a;
+      t.voff = epic::cov_slot(a) * ap;
+      t.row = cell[(size_t)a * g.KK] / N;
+      t.col = cell[(size_t)a * g.KK] % N;
+      for (int d = 0; d < K; ++d) {
+        t.wr[d] = own.wj[(size_t)a * K + d];
+        t.wc[d] = own.wx[(size_t)a * K + d];
+        t.fr[d] = (float)t.wr[d];
+        t.fc[d] = (float)t.wc[d];
+      }
+    }
+    std::fill(own.lanes.begin(), own.lanes.end(), idle);
+    if (g.transposed) own.wj.swap(own.wx);             // the builder goes by taps
+    if (!own.b.channel(c, own.wj.data(), own.wx.data(), &heads[(size_t)c * S::NW], own.lanes.data())) return false;
+    std::memcpy(&words[c * chan_words], own.lanes.data(), chan_words * 4);
+    return true;
+  });
 }
 
 // Time splits of the covariance kernel: its rounds of resident workgroups (0.9 us
@@ -1685,45 +1763,24 @@ void release_cov(epic_ctx* x) {
 }
 
 void build_cov(epic_ctx* x, const Geometry& g) {
-  const int C = x->cfg.n_chan, A = x->cfg.n_ant, N = x->cfg.grid_n, K = x->cfg.kernel_support, P = x->cfg.n_pol;
-  release_cov(x);                       // of the geometry before
-  if (!x->cov_allowed || !x->fused || N != 64 || K != 3 || x->cpx || A > 512) return;
+  const int C = x->cfg.n_chan, A = x->cfg.n_ant, N = x->cfg.grid_n, P = x->cfg.n_pol;
+  x->cov = false;                       // (what the geometry before held is used again below)
+  if (!x->cov_allowed || !x->fused || N != 64 || x->cfg.kernel_support != 3 || x->cpx || A > 512) return release_cov(x);
   x->cov_ap = (A + epic::kCovTile - 1) / epic::kCovTile * epic::kCovTile;
-  std::vector<epic::CovAnt> ants((size_t)C * A + epic::kCovAntsPast, epic::CovAnt{});
-  std::vector<int> order(A);
-  for (int c = 0; c < C; ++c) {
-    const int* cell = &g.tcell[(size_t)c * A * g.KK];
-    for (int a = 0; a < A; ++a) order[a] = a;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](int p, int q) { return cell[(size_t)p * g.KK] % N < cell[(size_t)q * g.KK] % N; });
-    for (int i = 0; i < A; ++i) {
-      epic::CovAnt& t = ants[(size_t)c * A + i];
-      const size_t o = (size_t)c * A + order[i];
-      t = epic::CovAnt{};
-      t.ant = order[i];
-      t.voff = epic::cov_slot(order[i]) * x->cov_ap;
-      t.row = g.tcell[o * g.KK] / N;
-      t.col = g.tcell[o * g.KK] % N;
-      for (int d = 0; d < K; ++d) {
-        t.wr[d] = (x->transposed ? g.wx : g.wj)[o * K + d];
-        t.wc[d] = (x->transposed ? g.wj : g.wx)[o * K + d];
-        t.fr[d] = (float)t.wr[d];
-        t.fc[d] = (float)t.wc[d];
-      }
-    }
-  }
+  std::vector<epic::CovAnt> ants;
   std::vector<epic::CovProgHead> heads;
   std::vector<uint32_t> prog;
   const bool many = A > epic::CovFold<2, false, epic::kCovPlain>::MAXA;
   x->cov_kind = many ? epic::kCovMany : epic::kCovPlain;
+  auto build = [&](auto shape) {
+    return build_cov_tables<decltype(shape)>(g, x->cov_ap, x->cfg.kernel_sigma_cells, ants, heads, prog);
+  };
+  using epic::CovFold;
   if (x->wide) {
-    if (many ? !build_cov_programs<epic::CovFold<2, true, epic::kCovMany>>(g, heads, prog)
-             : !build_cov_programs<epic::CovFold<2, true, epic::kCovPlain>>(g, heads, prog))
-      return;
-  } else if (many ? !build_cov_programs<epic::CovFold<2, false, epic::kCovMany>>(g, heads, prog)
-                  : !build_cov_programs<epic::CovFold<2, false, epic::kCovPlain>>(g, heads, prog)) {
+    if (many ? !build(CovFold<2, true, epic::kCovMany>{}) : !build(CovFold<2, true, epic::kCovPlain>{})) return release_cov(x);
+  } else if (many ? !build(CovFold<2, false, epic::kCovMany>{}) : !build(CovFold<2, false, epic::kCovPlain>{})) {
     x->cov_kind = epic::kCovCrowded;
-    if (!build_cov_programs<epic::CovFold<2, false, epic::kCovCrowded>>(g, heads, prog)) return;
+    if (!build(CovFold<2, false, epic::kCovCrowded>{})) return release_cov(x);
   }
   x->cov_fold_w = epic::covar::fold_blocks_per_cu(cov_shape(x)) * x->n_cu;
   // the gradient's shares per channel: whole rounds of resident workgroups, a
@@ -1747,11 +1804,11 @@ void build_cov(epic_ctx* x, const Geometry& g) {
                                 std::min(vg * C * kCovMaxParts, kCovSplitSpace)});
   x->cov_chan = (int)std::min<size_t>(C, have / vb);
   (void)hipGetLastError();
-  if (!x->cov_v.alloc(have) || !x->cov_r.alloc(cov_r_bytes(x, x->cov_chan)) ||
-      !x->cov_hat.alloc((size_t)x->cov_chan * P * N * N * sizeof(float4)) ||
-      !x->cov_gpart.alloc((size_t)x->cov_chan * P * x->cov_gchunks * x->cov_ggroups * x->PA * sizeof(double2)) ||
-      !x->cov_ants.alloc(ants.size() * sizeof(epic::CovAnt)) ||
-      !x->cov_head.alloc(heads.size() * sizeof(epic::CovProgHead)) || !x->cov_prog.alloc(prog.size() * 4) ||
+  if (!x->cov_v.reuse(have) || !x->cov_r.reuse(cov_r_bytes(x, x->cov_chan)) ||
+      !x->cov_hat.reuse((size_t)x->cov_chan * P * N * N * sizeof(float4)) ||
+      !x->cov_gpart.reuse((size_t)x->cov_chan * P * x->cov_gchunks * x->cov_ggroups * x->PA * sizeof(double2)) ||
+      !x->cov_ants.reuse(ants.size() * sizeof(epic::CovAnt)) ||
+      !x->cov_head.reuse(heads.size() * sizeof(epic::CovProgHead)) || !x->cov_prog.reuse(prog.size() * 4) ||
       hipMemcpy(x->cov_head.p, heads.data(), heads.size() * sizeof(epic::CovProgHead), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(x->cov_prog.p, prog.data(), prog.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(x->cov_ants.p, ants.data(), ants.size() * sizeof(epic::CovAnt), hipMemcpyHostToDevice) != hipSuccess) {
@@ -2511,7 +2568,11 @@ epic_status epic_set_antennas_kernels(epic_ctx* x, const double* xy_m, const dou
          hipMemcpy(x->taps_im.p, g.wi.data(), g.wi.size() * 4, hipMemcpyHostToDevice) != hipSuccess))
       return x->fail(EPIC_E_NOMEM, "gridding program upload failed");
     x->L = L;
-    build_cov(x, g);
+    try {
+      build_cov(x, g);
+    } catch (const std::bad_alloc&) {    // no host memory for its tables: the direct form alone
+      release_cov(x);
+    }
   } else {
     release_cov(x);
     if (!alloc_staged(x)) return x->fail(EPIC_E_NOMEM, "staged workspace allocation failed");
