@@ -82,7 +82,7 @@ void launch_hat(const CovHatArgs& a, int n_pol, int n_chan, hipStream_t stream) 
 }
 
 void launch_adjoint(const CovGradArgs& a, const Shape& s, hipStream_t stream) {
-  auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3((unsigned)a.total), dim3(512), 0, stream, a); };
+  auto go = [&](auto k) { hipLaunchKernelGGL(k, dim3((unsigned)a.total), dim3(64 * kCovGradWaves), 0, stream, a); };
 #define EPIC_CG(PP, WW) \
   if (s.n_pol == PP && s.wide == WW) go(cov_adjoint_kernel<PP, WW>);
   EPIC_CG(1, false) EPIC_CG(1, true) EPIC_CG(2, false) EPIC_CG(2, true)

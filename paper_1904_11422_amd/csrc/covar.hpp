@@ -69,8 +69,8 @@ __host__ __device__ __forceinline__ int cov_tiles(int nb, int P) {
 // imaginary part needs -im, which int8 cannot hold for 16 * (-8); the bitwise
 // complement of the nibble is -im - 1, exact, and the excess sum_t re_a is
 // taken from one dot product per operand.  132 channels of 256 dual-pol antennas,
-// T = 1000: 126 us (41 us of them, the covariances' 208 MB, whatever T is) =
-// 1.1 POP/s of 8 operations per pair and sample; 8.9 vector instructions per
+// T = 1000: 132 us (41 at T = 64: mostly the covariances' 208 MB written) =
+// 1.05 POP/s of 8 operations per pair and sample; 8.9 vector instructions per
 // matrix one, of which about 4 are free, so the two take turns (matrix pipes 25 %,
 // vector ALU 31 % busy).
 // Four antennas' samples are one load at any address (the hardware loads an
@@ -264,8 +264,7 @@ struct __align__(16) CovAnt {
   int voff;                 // its column in a plane of V, cov_slot(ant) * ap
   double wr[3];             // weights of rows row .. row + 2
   double wc[3];             // weights of columns col .. col + 2
-  float fr[3], fc[3];       // the same, rounded (the gradient's)
-  float pad1[2];
+  int lane, pad0[3];        // the gradient's lane of this index takes the antenna at index `lane`
 };
 
 constexpr int kCovAntsPast = 16;    // entries past the table that the fold's look-ahead may read
@@ -741,8 +740,8 @@ __device__ __forceinline__ void cov_fold_body(const CovFoldArgs& a, double2* con
 // column, Q_0 moves one lane on into Q_1 (the same d), so a sum stays in
 // registers until its last term and R is written once.
 // Bound: the chain of a step (an antenna's gridding, staging and folding between
-// two barriers; vector ALU 30 %, LDS 40 % of the cycles).  132 channels of 256
-// dual-pol antennas: 228 us, the wide block's 461 (the direct kernels take 1173 at
+// two barriers; vector ALU 32 %, LDS 41 % of the cycles).  132 channels of 256
+// dual-pol antennas: 235 us, the wide block's 461 (the direct kernels take 1173 at
 // T = 1000 and 1752 at T = 1250).  On the way, at 128 channels: whole rows per
 // wave instead of bands 260 against 244 us (wide 587 and 515); gridding at a raised
 // priority 240 (469), as LDS and vector ALU are then wanted by different waves;

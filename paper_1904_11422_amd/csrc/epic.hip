@@ -1721,9 +1721,25 @@ bool build_cov_tables(const Geometry& g, int ap, double sigma, std::vector<epic:
       for (int d = 0; d < K; ++d) {
         t.wr[d] = own.wj[(size_t)a * K + d];
         t.wc[d] = own.wx[(size_t)a * K + d];
-        t.fr[d] = (float)t.wr[d];
-        t.fc[d] = (float)t.wc[d];
       }
+    }
+    // the gradient's lanes: by 16, one antenna of each place in the table modulo 16
+    // (its rows are 65 or 63 places of 16 bytes), the fullest residues first
+    std::vector<int> by[16];
+    for (int i = A - 1; i >= 0; --i) {
+      const epic::CovAnt& t = ants[(size_t)c * A + i];
+      by[(t.row * (g.wide_rows ? 65 : 63) + t.col) % 16].push_back(i);
+    }
+    bool used[16];
+    for (int l = 0; l < A; ++l) {
+      if (l % 16 == 0) std::fill(used, used + 16, false);
+      int r = -1;
+      for (int pass = 0; pass < 2 && r < 0; ++pass)
+        for (int k = 0; k < 16; ++k)
+          if (!by[k].empty() && (pass || !used[k]) && (r < 0 || by[k].size() > by[r].size())) r = k;
+      used[r] = true;
+      ants[(size_t)c * A + l].lane = by[r].back();
+      by[r].pop_back();
     }
     std::fill(own.lanes.begin(), own.lanes.end(), idle);
     if (g.transposed) own.wj.swap(own.wx);             // the builder goes by taps
@@ -1787,9 +1803,9 @@ void build_cov(epic_ctx* x, const Geometry& g) {
   // share costing its pairs and about four more steps (the table of H)
   const int atiles = (A + 63) / 64;
   double best = 0;
-  x->cov_ggroups = 8 / atiles;
+  x->cov_ggroups = epic::kCovGradWaves / atiles;
   for (int n = 1; n <= 16; ++n) {
-    const double t = (double)(((int64_t)C * P * n + 2 * x->n_cu - 1) / (2 * x->n_cu)) *
+    const double t = (double)(((int64_t)C * P * n + x->n_cu - 1) / x->n_cu) *
                      ((double)A / (n * x->cov_ggroups) + 4);
     if (n == 1 || t < best) {
       best = t;
@@ -1805,7 +1821,7 @@ void build_cov(epic_ctx* x, const Geometry& g) {
   x->cov_chan = (int)std::min<size_t>(C, have / vb);
   (void)hipGetLastError();
   if (!x->cov_v.reuse(have) || !x->cov_r.reuse(cov_r_bytes(x, x->cov_chan)) ||
-      !x->cov_hat.reuse((size_t)x->cov_chan * P * N * N * sizeof(float4)) ||
+      !x->cov_hat.reuse((size_t)x->cov_chan * P * N * N * P * sizeof(double2)) ||
       !x->cov_gpart.reuse((size_t)x->cov_chan * P * x->cov_gchunks * x->cov_ggroups * x->PA * sizeof(double2)) ||
       !x->cov_ants.reuse(ants.size() * sizeof(epic::CovAnt)) ||
       !x->cov_head.reuse(heads.size() * sizeof(epic::CovProgHead)) || !x->cov_prog.reuse(prog.size() * 4) ||
@@ -1871,25 +1887,26 @@ bool use_cov(const epic_ctx* x, int64_t n_time) {
 }
 
 // The same for the gradient, whose covariance form costs every channel its
-// pairs of antennas, in tiles of 64 by what a workgroup's eight waves hold of them
-// (kept whole: five tiles leave three waves idle).  Fitted to 6397 calls, likewise:
-// 0.1 % slower by over 3 %, the worst by 11 %.  256 dual-pol antennas: 412 us direct, 83 here at 16
-// channels of 1250 samples, 304 / 150 at 64 of 200, 41 / 52 at 2 of 200.
+// pairs of antennas, in tiles of 64 by what a workgroup's waves hold of them (whole
+// groups: five tiles leave one wave of 16 idle), and the passes over its
+// covariances.  Fitted to 9250 calls, likewise: at most 0.3 % slower by over 3 %,
+// the worst by 19 %.  E.g. dual-pol: 294 us direct, 75 here at 252 antennas, 16
+// channels, T = 960; 233 / 120 at 240, 44, 243; 23 / 46 at 236, 2, 196.
 bool use_cov_backward(const epic_ctx* x, int64_t n_time) {
   if (!cov_takes(x, n_time)) return false;
   struct Fit {
     double one, ct, cta, few;            // direct, as above
-    double cone, ca, cc, pairs;          // covariance: per antenna, channel, 512 lanes' pairs with one b
+    double cone, ca, mb, pairs;          // covariance: per antenna, MB of V, 1024 lanes' pairs with one b
   };
-  static const Fit fits[2][2] = {{{14.7, 9.19e-3, 0.90e-5, 0.8e-3, 13.4, 0.035, 0.031, 3.67e-3},
-                                  {15.0, 10.19e-3, 1.09e-5, 0.7e-3, 12.6, 0.025, 0.029, 2.92e-3}},
-                                 {{15.5, 14.38e-3, 2.35e-5, 2.2e-3, 21.7, 0.011, 0.109, 8.97e-3},
-                                  {16.4, 15.82e-3, 3.82e-5, 2.4e-3, 21.2, 0.013, 0.099, 9.15e-3}}};
+  static const Fit fits[2][2] = {{{15.1, 9.17e-3, 0.87e-5, 0.7e-3, 17.0, 0.008, 0.0, 5.82e-3},
+                                  {15.3, 10.05e-3, 1.04e-5, 0.8e-3, 16.3, 0.014, 0.0, 5.89e-3}},
+                                 {{15.7, 14.27e-3, 2.29e-5, 2.2e-3, 29.0, 0.0, 0.137, 19.5e-3},
+                                  {16.7, 15.77e-3, 3.81e-5, 2.3e-3, 29.4, 0.0, 0.134, 20.2e-3}}};
   const Fit& f = fits[x->cfg.n_pol - 1][x->wide];
   const double C = x->cfg.n_chan, A = x->cfg.n_ant, ct = C * (double)n_time;
   const double direct = f.one + ct * (f.ct + f.cta * A) + f.few * std::min(ct, 4096.0);
   const CovCorrCost k = cov_corr_cost(x, n_time);
-  const double cov = f.cone + f.ca * A + C * (f.cc + f.pairs * A / x->cov_ggroups) +
+  const double cov = f.cone + f.ca * A + C * (1e-6 * f.mb * cov_v_bytes(x) + f.pairs * A / x->cov_ggroups) +
                      (A < 4 ? 4.5 : x->cfg.n_ant % 4 ? 1.95 : 1.45) * k.stages + 0.65 * k.mb;
   return cov_faster(cov, direct);
 }
@@ -2004,7 +2021,7 @@ epic_status cov_backward(epic_ctx* x, const uint8_t* efield, int64_t n_time, con
     const epic::CovCorrArgs ca = launch_cov_corr(x, plan, efield, n_time, c0, nc, n_prod);
     epic::CovHatArgs ha;
     ha.grad_image = reinterpret_cast<const double2*>(grad_image);
-    ha.hat = x->cov_hat.as<float2>();
+    ha.hat = x->cov_hat.as<double2>();
     ha.c0 = c0;
     ha.transposed = x->transposed ? 1 : 0;
     epic::covar::launch_hat(ha, P, nc, x->stream);
@@ -2012,7 +2029,7 @@ epic_status cov_backward(epic_ctx* x, const uint8_t* efield, int64_t n_time, con
     ga.v = ca.v;
     ga.gains = reinterpret_cast<const float2*>(gains);
     ga.ants = x->cov_ants.as<epic::CovAnt>();
-    ga.hat = x->cov_hat.as<float4>();
+    ga.hat = x->cov_hat.as<double2>();
     ga.part = x->cov_gpart.as<double2>();
     ga.n_ant = A;
     ga.ap = x->cov_ap;

@@ -169,3 +169,27 @@ def test_gains_of_any_scale(scale):
     err = oracle.rel_errors(got / scale ** 2, want).max()
     print(f"  scale {scale:.0e}: {err:.2e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("seed,A,P,fill", [(942, 256, 2, 0.45), (943, 200, 1, 0.45), (944, 200, 2, 0.66), (945, 300, 2, 0.48)])
+def test_gradient_of_dark_pixels(seed, A, P, fill):
+    """A loss that looks at one pixel far below the peak: the sum over antennas
+    cancels as deeply as the field does there.  Float64 up to the gradient's own
+    rounding to float32 (6e-8 of an element): 2e-7 of its norm."""
+    import torch
+    from test_covar_shapes_gpu import _gradient
+    inp = _coherent(synth.random_problem(seed, 64, A, 40, P, 900, fill=fill), seed)
+    im = _imager(inp)
+    ef, g = _dev(inp)
+    sub = _channel(inp, 0)
+    power = oracle.image_from(sub)[0, 0].real
+    order = np.argsort(power.ravel())
+    for rank in (0, 40, 400, 4095):
+        gam = np.zeros(im.image_shape(), np.complex128)
+        gam.reshape(40, -1, 4096)[:, :, order[rank]] = 1
+        got = im.backward(ef, g, torch.from_numpy(gam).cuda()).cpu().numpy()
+        assert im.last_form() == "covariance"
+        want = _gradient(sub, gam[0])
+        err = np.linalg.norm(got[:1] - want) / np.linalg.norm(want)
+        print(f"  A={A} P={P} pixel at {power.ravel()[order[rank]] / power.max():.1e} of the peak: {err:.1e}", flush=True)
+        assert err <= 2e-7
