@@ -6,9 +6,10 @@ dual-polarisation antennas, 132 channels, a 64 x 64 grid and 1000 samples per
 channel, giving 132 accumulated 4-polarisation channel images.  Inputs are
 synthetic (seeded) and resident in HBM before the timed region.
 
-Prints one JSON line.  `value` is channel-images/s of the fused kernel path;
-the plain float32 staged path (one kernel per stage, intermediates in HBM) is
-reported beside it, and the FP64 CPU oracle is timed on a bounded sample.
+Prints one JSON line.  `value` is channel-images/s of the route a caller gets;
+the direct form (a transform per sample) and the plain float32 staged path
+(one kernel per stage, intermediates in HBM) are reported beside it, and the
+FP64 CPU oracle is timed on a bounded sample.
 """
 from __future__ import annotations
 
@@ -223,20 +224,20 @@ def covariance_ops(P, A) -> int:
     return 8 * (A * (A + 1) + A * A if P == 2 else A * (A + 1) // 2)
 
 
-def image_roofline(kernel, N, P, A, C, T, k_ms) -> dict:
+def image_roofline(form, N, P, A, C, T, k_ms) -> dict:
     """The image kernels' rate against the unit that bounds them: the direct
     kernels by the direct method's flops on the vector ALU; the covariance form
     (all its kernels in k_ms) by its integer products on the matrix cores, since
     it does not transform every sample."""
     fl = flops_per_tc(N, P, A)
-    if kernel == "cov_fold_kernel":
+    if form == "covariance":
         ops = covariance_ops(P, A)
         rate = ops * C * T / (k_ms * 1e-3)
         return {"bound": "mfma", "form": "covariance", "achieved": rate / 1e12, "peak": PEAK_MFMA_I8 / 1e12,
                 "unit": "TOP/s", "frac": rate / PEAK_MFMA_I8, "traffic": None, "int8_ops_per_tc": ops,
                 "direct_method_flops_per_tc_image": fl}
     rate = fl * C * T / (k_ms * 1e-3)
-    return {"bound": "alu", "form": "direct", "achieved": rate / 1e12, "peak": PEAK_FP32_VALU / 1e12,
+    return {"bound": "alu", "form": form, "achieved": rate / 1e12, "peak": PEAK_FP32_VALU / 1e12,
             "unit": "TFLOP/s", "frac": rate / PEAK_FP32_VALU,
             "frac_nonpacked": rate / PEAK_FP32_VALU_NONPACKED, "traffic": None, "flops_per_tc_image": fl}
 
@@ -326,28 +327,36 @@ def grad_results(steps: int, warmup: int) -> dict:
     t0 = time.perf_counter()
     for _ in range(steps):
         im.accumulate(ef, g, image=img)
-        fname = im.last_kernel_name()
+        fname, fform = im.last_kernel_name(), im.last_form()
         im.backward(ef, g, gam)
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / steps
     hist = im.timing_history(2 * steps)          # forward and adjoint kernels, alternating
     fw, bw = hist[0::2], hist[1::2]
-    bname = im.last_kernel_name()
+    bname, bform = im.last_kernel_name(), im.last_form()
     im.close()
-    # the covariance form, which this shape takes: its integer products, and for
-    # every pair of antennas and product 25 complex values times a real weight
-    # (4 flop each), five row sums (4) and the pair's complex products (22)
     adj_s = float(np.mean(bw)) * 1e-3
-    fl_adj = P * P * A * A * (25 * 4 + 5 * 4 + 22)
+    if bform == "covariance":
+        # its integer products, and in float64 (the non-packed float32 rate), for
+        # every pair of antennas and product, 25 complex values times a real weight
+        # (4 flop each), five row sums (4) and the pair's complex products (14)
+        fl_adj = P * P * A * A * (25 * 4 + 5 * 4 + 14)
+        rate, peak = fl_adj * C / adj_s, PEAK_FP32_VALU_NONPACKED
+        roofline = {"bound": "lds", "flops_per_channel": fl_adj, "int8_ops_per_tc": covariance_ops(P, A)}
+    else:
+        # per (t,c): the forward recompute without the products, dL/dF* (20 flop per
+        # pixel at P = 2), the adjoint transform, the degridding
+        fl_adj = (flops_per_tc(N, P, A) - 16 * N * N + 20 * N * N + P * 5 * N * N * int(math.log2(N * N))
+                  + (4 * 9 + 6) * P * A)
+        rate, peak = fl_adj * C * T / adj_s, PEAK_FP32_VALU
+        roofline = {"bound": "alu", "flops_per_tc_image": fl_adj,
+                    "frac_nonpacked": rate / PEAK_FP32_VALU_NONPACKED}
     return {"value": 1.0 / dt, "unit": "evaluations/s", "ms_per_step": dt * 1e3, "steps": steps,
-            "forward_kernel": fname, "forward_kernel_ms": float(np.mean(fw)),
+            "forward_kernel": fname, "forward_form": fform, "forward_kernel_ms": float(np.mean(fw)),
             "adjoint_kernel_ms": adj_s * 1e3,
             "adjoint_tc_images_per_s": C * T / adj_s,
-            "roofline": {"bound": "lds", "form": "covariance", "kernel": bname,
-                         "achieved": fl_adj * C / adj_s / 1e12, "peak": PEAK_FP32_VALU / 1e12,
-                         "unit": "TFLOP/s", "frac": fl_adj * C / adj_s / PEAK_FP32_VALU,
-                         "frac_nonpacked": fl_adj * C / adj_s / PEAK_FP32_VALU_NONPACKED,
-                         "flops_per_channel": fl_adj, "int8_ops_per_tc": covariance_ops(P, A)},
+            "roofline": {**roofline, "form": bform, "kernel": bname, "achieved": rate / 1e12,
+                         "peak": peak / 1e12, "unit": "TFLOP/s", "frac": rate / peak},
             "workload": "256 dual-pol antennas, 64 channels, 64x64 grid, 200 samples, "
                         "20 sources"}
 
@@ -398,7 +407,7 @@ def autos_results(steps: int, warmup: int, inp=None) -> dict:
         im.accumulate(ef, g, image=img)
     torch.cuda.synchronize()
     cov_dt = (time.perf_counter() - t0) / steps
-    cov_kernel = im.last_kernel_name()
+    cov_kernel, cov_form = im.last_kernel_name(), im.last_form()
     nq = 4 if P == 2 else 1
     # algorithmic bytes of the sum pass: every sample byte once, the exact
     # per-antenna sums (nq int32) out once
@@ -413,7 +422,7 @@ def autos_results(steps: int, warmup: int, inp=None) -> dict:
                       "grid_n": N, "n_chan": C, "n_pol": P, "n_ant": A, "n_time": T},
            "imager_kernel_ms": float(np.mean(main_ms)), "auto_sum_kernel_ms": s_ms,
            "removal_ms": float(np.mean(rem_ms)),
-           "default_route": {"kernel": cov_kernel, "ms_per_step": cov_dt * 1e3, "value": C / cov_dt},
+           "default_route": {"kernel": cov_kernel, "form": cov_form, "ms_per_step": cov_dt * 1e3, "value": C / cov_dt},
            "roofline": {"bound": "hbm", "kernel": "auto_sum_kernel",
                         "achieved": alg / (s_ms * 1e-3) / 1e9, "peak": PEAK_HBM / 1e9,
                         "unit": "GB/s", "frac": alg / (s_ms * 1e-3) / PEAK_HBM,
@@ -585,7 +594,7 @@ def deployment_results(steps: int, warmup: int, inp=None) -> dict:
         dt = (time.perf_counter() - t0) / steps
         ks = im.timing_history(steps)
         k_ms = float(np.mean(ks))
-        kname = im.last_kernel_name()              # the image kernel, before the gradient runs
+        kname, form = im.last_kernel_name(), im.last_form()   # the image's, before the gradient runs
         # one gain-gradient evaluation (image + adjoint) per call, same route
         gam = torch.randn(im.image_shape(), dtype=torch.complex128, device="cuda")
         im.backward(ef, g, gam)
@@ -596,12 +605,12 @@ def deployment_results(steps: int, warmup: int, inp=None) -> dict:
             im.backward(ef, g, gam)
         torch.cuda.synchronize()
         grad_ms = (time.perf_counter() - t1) / nb * 1e3
-        grad_kernel = im.last_kernel_name()
+        grad_kernel, grad_form = im.last_kernel_name(), im.last_form()
         out["staged" if staged else "fused"] = {
-            "gradient_ms_per_call": grad_ms, "gradient_kernel": grad_kernel,
+            "gradient_ms_per_call": grad_ms, "gradient_kernel": grad_kernel, "gradient_form": grad_form,
             "value": C / dt, "unit": "channel-images/s", "ms_per_step": dt * 1e3, "steps": steps,
             "kernel": kname, "kernel_ms": k_ms,
-            "roofline": image_roofline(kname, N, P, A, C, T, k_ms)}
+            "roofline": image_roofline(form, N, P, A, C, T, k_ms)}
         im.close()
     main = out["fused"]
     main["speedup_over_staged"] = main["value"] / out["staged"]["value"]
@@ -658,7 +667,7 @@ def bench_arrays(args) -> int:
         out[f"a{A}"] = {"bytes_per_thread": -(-P * A // 512), "kernel": im.last_kernel_name(),
                         "kernel_ms": k_ms, "ms_per_step": dt * 1e3, "value": C / dt,
                         "tc_images_per_s": C * T / (k_ms * 1e-3),
-                        "roofline": image_roofline(im.last_kernel_name(), N, P, A, C, T, k_ms)}
+                        "roofline": image_roofline(im.last_form(), N, P, A, C, T, k_ms)}
         im.close()
     main = out["a1024"]
     line = {"metric": "channel-images/s for denser arrays (64\u00b2 grid)", "value": main["value"],
@@ -870,7 +879,7 @@ def main() -> int:
     for _ in range(args.warmup):
         im.accumulate(ef, g, image=img, reset=True)
     torch.cuda.synchronize()
-    print("bench: timing the fused path", file=sys.stderr, flush=True)
+    print("bench: timing the default route", file=sys.stderr, flush=True)
 
     t0 = time.perf_counter()
     for _ in range(args.steps):
@@ -882,10 +891,12 @@ def main() -> int:
     kernel_ms = im.timing_history(args.steps)
     ms_per_step = dt * 1e3 / args.steps
     value = C * args.steps / dt
-    kname = im.last_kernel_name()
+    kname, form = im.last_kernel_name(), im.last_form()
 
     k_ms = float(np.mean(kernel_ms))
-    roofline = {**image_roofline(kname, N, P, A, C, T, k_ms), "clock_ghz_measured": measured_clock(),
+    # the clock measured is that under the direct kernel
+    roofline = {**image_roofline(form, N, P, A, C, T, k_ms),
+                "clock_ghz_measured": measured_clock() if form == "direct" else None,
                 "kernel": kname, "kernel_ms": k_ms, "input_bytes_per_launch": C * T * P * A}
 
     # the direct form (a transform per sample and channel), through the
@@ -901,8 +912,8 @@ def main() -> int:
     d_ms = float(np.mean(im.timing_history(args.steps)))
     direct = {"value": C * args.steps / dt_direct, "unit": "channel-images/s",
               "ms_per_step": dt_direct * 1e3 / args.steps, "tc_images_per_s": C * T * args.steps / dt_direct,
-              "roofline": {**image_roofline(im.last_kernel_name(), N, P, A, C, T, d_ms),
-                           "traffic": measured_traffic(), "kernel": im.last_kernel_name(), "kernel_ms": d_ms}}
+              "roofline": {**image_roofline(im.last_form(), N, P, A, C, T, d_ms),
+                           "clock_ghz_measured": measured_clock(), "traffic": measured_traffic(), "kernel": im.last_kernel_name(), "kernel_ms": d_ms}}
     im.close()
     if staged is not None:
         staged["speedup_of_fused"] = value / staged["value"]

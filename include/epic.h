@@ -106,8 +106,12 @@ epic_status epic_set_stream(epic_ctx *ctx, void *hip_stream);
 /* Set the array geometry (Sec. 3.2 and Sec. 4.2: gridding at a fixed fraction
  * of each channel's wavelength).  xy_m: host float64 [n_ant][2] (east, north)
  * in metres; freq_hz: host float64 [n_chan].  Builds the per-channel kernel
- * weights (in float64, rounded once to float32) and the gridding tables and
- * uploads them before returning (synchronous).  May be called again.
+ * weights (in float64, rounded once to float32; the covariance form below uses
+ * them unrounded) and the gridding tables and uploads them before returning
+ * (synchronous).  May be called again.  Where calls may take the covariance form
+ * (grid_n = 64, kernel_support = 3, at most 512 antennas) the context then also
+ * holds that form's workspace: at most 384 MB of covariances and their partial
+ * sums, less where the channels need less.
  * Errors: EPIC_E_INVALID (null, non-finite position, frequency not finite and
  * positive), EPIC_E_OFFGRID (a tap outside [0, N) for some channel; the
  * previous geometry, if any, stays in force), EPIC_E_NOMEM. */
@@ -170,16 +174,26 @@ epic_status epic_gridding_program(const epic_config *cfg, const double *xy_m,
  *           fftshifted; reset != 0 overwrites it, reset == 0 adds to it, so an
  *           integration can be split over several calls.
  * XX and YY are written with a zero imaginary part (reset != 0) or have their
- * imaginary part left unchanged (reset == 0).  Accumulation is float64;
- * the per-sample transform is float32 (EPIC_FP32) or split float16 / bfloat16
- * matrix products with float32 accumulation (EPIC_SPLIT_*).  Allocates nothing.
+ * imaginary part left unchanged (reset == 0).  The direct form transforms every
+ * sample, in float32 (EPIC_FP32) or split float16 / bfloat16 matrix products
+ * with float32 accumulation (EPIC_SPLIT_*), and accumulates in float64 (blocks of
+ * at most 128 samples in float32 first).  Where it is estimated to be faster --
+ * EPIC_FP32, grid_n = 64, 3 x 3 Gaussian kernels, at most 512 antennas, 64 to
+ * 131072 samples -- the call takes the covariance form instead: the antennas'
+ * time-summed covariances, exact in integers, are gridded and transformed once
+ * per channel, in float64.  The choice depends on the configuration, the
+ * geometry and n_time only, not on the data or its address; both forms agree
+ * to the direct form's float32 rounding, and what a call adds to XX and YY is
+ * nowhere negative in either (with EPIC_FLAG_REMOVE_AUTOS it may be).
+ * epic_last_form tells which one ran.  Allocates nothing.
  * With EPIC_FLAG_REMOVE_AUTOS (Sec. 3.2 and Fig. 2: the optional removal of
  * the zero-spacing power, done after squaring and accumulation) the call then
  * subtracts the a = b terms of the visibility form of the image,
  *   sum_a V_PQ[a] |b_a(k)|^2,  V_PQ[a] = g_P conj(g_Q) sum_t e_P[t,a] conj(e_Q[t,a]),
  * b_a(k) the transform of antenna a's kernel taps: the integer sums are exact
- * and the rest is float64.  It adds two passes: one more read of efield and a
- * read-modify-write of image.  Only the samples of this call are removed, so
+ * and the rest is float64.  On the direct form it adds two passes, one more
+ * read of efield and a read-modify-write of image; the covariance form leaves the
+ * terms out of its sums.  Only the samples of this call are removed, so
  * split integrations stay consistent; a call takes at most 2^24 - 1 samples
  * with the flag (more: EPIC_E_UNSUPPORTED).
  * Errors: EPIC_E_STATE (no antennas), EPIC_E_INVALID (null pointer,
@@ -189,8 +203,8 @@ epic_status epic_image_accumulate(epic_ctx *ctx, const uint8_t *efield, int64_t 
 
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * imaging call as epic_image_accumulate, with the same arguments, ownership,
- * product order and result, but its partial-image slots live in a static
+ * imaging call as epic_image_accumulate, with the same arguments, ownership
+ * and product order, but its partial-image slots live in a static
  * device array of the library (96 MiB, held by each device the library runs
  * on until the process ends) instead of the context's workspace.  The call
  * allocates nothing and runs the fused float32 kernels only (grid_n 32, 64
@@ -201,8 +215,9 @@ epic_status epic_image_accumulate(epic_ctx *ctx, const uint8_t *efield, int64_t 
  * device's array: calls that overlap in time on one device (any contexts,
  * any streams) race, so serialise them.  Nothing needs clearing between
  * calls (each call writes its slots before it reads them).
- * It runs the direct kernels for every n_time; epic_image_accumulate may take
- * the covariance form for long integrations, equal to within float32 rounding.
+ * It runs the direct form for every n_time: bits as epic_image_accumulate's where
+ * that call is direct too, and equal to within float32 rounding where it takes
+ * the covariance form.
  * Errors: as epic_image_accumulate; EPIC_E_UNSUPPORTED for the staged and
  * split paths and for calls whose slots exceed the array; EPIC_E_DEVICE when
  * the array has no address on this device. */
@@ -221,8 +236,10 @@ epic_status epic_image_accumulate_noalloc(epic_ctx *ctx, const uint8_t *efield, 
  *               are real);
  *   grad_gains: device complex64 [n_chan][n_pol][n_ant], overwritten with
  *               dL/dRe(g) + i dL/dIm(g).
- * The per-sample transforms are recomputed, not stored; the reduction over
- * time is float64.  With EPIC_FLAG_REMOVE_AUTOS the loss is that of the image
+ * Nothing is kept from the forward call: the direct form recomputes the
+ * per-sample transforms (float32) and sums over time in float64; the covariance
+ * form, chosen as there but by its own estimate, recomputes the covariances and
+ * sums over antenna pairs in float64.  With EPIC_FLAG_REMOVE_AUTOS the loss is that of the image
  * without the autocorrelation terms.  Runs wherever the float32 image runs:
  * the fused kernels (grid_n 32, 64 and 128) or the staged ones
  * (EPIC_FLAG_STAGED, or a channel's taps outside an N/2 x N/2 block).
@@ -260,7 +277,8 @@ epic_status epic_kernel_taper(epic_ctx *ctx, double *taper);
 
 /* With EPIC_FLAG_TIMING: wait for the last imaging call and report the
  * duration of its main kernel and of the whole call, in milliseconds, measured
- * with HIP events on the context's stream.  Errors: EPIC_E_STATE (no timed
+ * with HIP events on the context's stream.  The covariance form's kernels count
+ * as one main kernel, from the first to the last.  Errors: EPIC_E_STATE (no timed
  * call yet or flag not set). */
 epic_status epic_last_timing(epic_ctx *ctx, float *main_kernel_ms, float *call_ms);
 
@@ -277,7 +295,9 @@ epic_status epic_timing_history(epic_ctx *ctx, int32_t n, float *main_ms);
 /* With EPIC_FLAG_TIMING and EPIC_FLAG_REMOVE_AUTOS: wait for the last imaging
  * call and report the duration of its autocorrelation-sum kernel (the pass
  * over efield) and of the whole removal (sums, table and subtraction), in
- * milliseconds.  Errors: EPIC_E_STATE (no such call yet). */
+ * milliseconds.  Where the call took the covariance form, which has no such
+ * passes, both are the time between two events with nothing in between.
+ * Errors: EPIC_E_STATE (no such call yet). */
 epic_status epic_last_autos_timing(epic_ctx *ctx, float *sum_kernel_ms, float *removal_ms);
 
 /* Name of the main kernel the last imaging or gradient call launched (static
